@@ -99,7 +99,7 @@ struct BField {
 // Workspace layout of a plan (byte offsets).
 struct Layout {
   uint64_t head, fields, items_q, items_d, items_f, params, done, state, groups, counts, stage,
-      partials, dstatus, args, total;
+      partials, dstatus, total;
   uint64_t clear_begin, clear_words;  // u64 words zeroed before each quantize
 };
 
@@ -118,25 +118,20 @@ struct BatchQArgs {
   unsigned ready_polls;  // NOA parameter-flag polls before deriving them directly
 };
 
-// Values the caller knows are the same on every lane, moved to scalar
-// registers (so the loads they address become scalar loads).
-template <typename P> __device__ __forceinline__ P *uni_ptr(P *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint64_t lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-  const uint64_t hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return reinterpret_cast<P *>(lo | (hi << 32));
-}
-// Copy of a descriptor every lane reads at the same address, word by word
-// into scalar registers.  (The kernel writes global memory, so the compiler
-// cannot prove these loads unclobbered and would otherwise keep every field
-// of the descriptor, and everything computed from it, in vector registers.)
+// Copy of a descriptor that every lane reads at the same address, through
+// the constant address space: plan data that no kernel writes, so its loads
+// are scalar loads into scalar registers.  (As ordinary loads they are
+// vector loads -- the kernel writes global memory, so the compiler cannot
+// prove them unclobbered -- and the 62 words of a field took the quantize
+// kernel to 108 vector registers, 4 wavefronts per SIMD.)
 template <typename S> __device__ __forceinline__ S uload(const S *p) {
   static_assert(sizeof(S) % 4 == 0, "descriptor of whole words");
+  typedef const __attribute__((address_space(4))) unsigned cword;
+  const cword *src = (const cword *)p;
   S out;
   unsigned w[sizeof(S) / 4];
-  __builtin_memcpy(w, p, sizeof(S));
 #pragma unroll
-  for (unsigned k = 0; k < sizeof(S) / 4; k++) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+  for (unsigned k = 0; k < sizeof(S) / 4; k++) w[k] = src[k];
   __builtin_memcpy(&out, w, sizeof(S));
   return out;
 }
@@ -273,7 +268,8 @@ __device__ __forceinline__ void tile_item(const BatchQArgs &a, const BField &bf,
 
 // Chunk variant, pass 1: the workgroup's 4 chunks of one field.
 template <typename T, int Q>
-__device__ __forceinline__ void chunk_item(const BatchQArgs &a, const BField &bf, uint64_t tile) {
+__device__ __forceinline__ void chunk_item(const BatchQArgs &a, const BField &bf, uint64_t tile,
+                                           void *s_stage, unsigned *s_cnt) {
   using U = typename FT<T>::U;
   StageField<T> f;
   f.in = static_cast<const T *>(bf.in);
@@ -284,7 +280,8 @@ __device__ __forceinline__ void chunk_item(const BatchQArgs &a, const BField &bf
   f.group = reinterpret_cast<unsigned long long *>(a.ws + bf.group_off);
   f.tiles_per_group = bf.tiles_per_group;
   f.p = field_params<T, Q>(a, bf, nullptr);
-  quant_chunks_n<T, Q>(f, tile, (unsigned)bf.cpw);
+  quant_chunks_n<T, Q>(f, tile, (unsigned)bf.cpw, static_cast<U (*)[stage_cap<T>()]>(s_stage),
+                       s_cnt);
 }
 
 // One workgroup per work item, in queue order: the hardware dispatcher hands
@@ -294,8 +291,7 @@ __device__ __forceinline__ void chunk_item(const BatchQArgs &a, const BField &bf
 // outlier count) is bounded with a fallback that computes the awaited value
 // from the input, so no dispatch order can stall the grid.
 template <int SL32, int RD32, int SL64, int RD64, bool CHUNK>
-__global__ __launch_bounds__(kBlock) void k_batch_quantize(const BatchQArgs *ap) {
-  const BatchQArgs a = uload(ap);
+__global__ __launch_bounds__(kBlock) void k_batch_quantize(BatchQArgs a) {
   const unsigned cur = blockIdx.x;
   const uint64_t it = uload(a.items + cur);
   const BField f = uload(a.fields + (it >> 32));
@@ -306,14 +302,19 @@ __global__ __launch_bounds__(kBlock) void k_batch_quantize(const BatchQArgs *ap)
     return;
   }
   if constexpr (CHUNK) {
+    // one stage area for all six instantiations (quant_chunks_n)
+    __shared__ uint64_t s_stage[kWaves * stage_cap<double>()];
+    __shared__ unsigned s_cnt[kWaves];
+    static_assert(sizeof(float) * stage_cap<float>() <= sizeof(double) * stage_cap<double>(),
+                  "the float64 rows hold the float32 ones");
     if (f.dtype == LCQ_F32) {
-      if (f.q == kABS) chunk_item<float, kABS>(a, f, local);
-      else if (f.q == kREL) chunk_item<float, kREL>(a, f, local);
-      else chunk_item<float, kNOA>(a, f, local);
+      if (f.q == kABS) chunk_item<float, kABS>(a, f, local, s_stage, s_cnt);
+      else if (f.q == kREL) chunk_item<float, kREL>(a, f, local, s_stage, s_cnt);
+      else chunk_item<float, kNOA>(a, f, local, s_stage, s_cnt);
     } else {
-      if (f.q == kABS) chunk_item<double, kABS>(a, f, local);
-      else if (f.q == kREL) chunk_item<double, kREL>(a, f, local);
-      else chunk_item<double, kNOA>(a, f, local);
+      if (f.q == kABS) chunk_item<double, kABS>(a, f, local, s_stage, s_cnt);
+      else if (f.q == kREL) chunk_item<double, kREL>(a, f, local, s_stage, s_cnt);
+      else chunk_item<double, kNOA>(a, f, local, s_stage, s_cnt);
     }
   } else {
     if (f.dtype == LCQ_F32) {
@@ -350,8 +351,7 @@ __device__ __forceinline__ void finish_item(const BatchQArgs &a, const BField &b
   quant_finish<T>(f, g);
 }
 
-__global__ __launch_bounds__(kBlock) void k_batch_finish(const BatchQArgs *ap) {
-  const BatchQArgs a = uload(ap);
+__global__ __launch_bounds__(kBlock) void k_batch_finish(BatchQArgs a) {
   const uint64_t it = uload(a.items_f + blockIdx.x);
   const BField f = uload(a.fields + (it >> 32));
   const uint64_t g = it & 0xFFFFFFFFull;
@@ -393,9 +393,9 @@ __device__ void deq_item(const BatchDArgs &a, const BField &bf, uint32_t fi, uin
 }
 
 __global__ __launch_bounds__(kBlock) void k_batch_dequantize(BatchDArgs a) {
-  const uint64_t it = a.items[blockIdx.x];
+  const uint64_t it = uload(a.items + blockIdx.x);
   const uint32_t fi = (uint32_t)(it >> 32);
-  const BField &f = a.fields[fi];
+  const BField f = uload(a.fields + fi);
   const uint64_t tile = it & 0xFFFFFFFFull;
   if (f.dtype == LCQ_F32) deq_item<float>(a, f, fi, tile);
   else deq_item<double>(a, f, fi, tile);
@@ -481,7 +481,6 @@ Layout layout_for(const Counts &c, uint32_t nf) {
   L.groups = o;        o += up256(8 * std::max<uint64_t>(c.group_words, 1));
   L.clear_begin = 0;
   L.clear_words = o / 8;  // head, params (ready flags), done, status, state, group sums
-  L.args = o;          o += up256(sizeof(BatchQArgs));
   L.fields = o;        o += up256(sizeof(BField) * std::max<uint32_t>(nf, 1));
   L.items_q = o;       o += up256(8 * std::max<uint64_t>(c.n_a + c.n_b, 1));
   L.items_d = o;       o += up256(8 * std::max<uint64_t>(c.n_d, 1));
@@ -525,7 +524,7 @@ Tune parse_tune(const char *tune) {
   return t;
 }
 
-lcq_status launch_batch_quantize(int bv, const BatchQArgs *a, unsigned grid, hipStream_t s) {
+lcq_status launch_batch_quantize(int bv, const BatchQArgs &a, unsigned grid, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
   switch (bv) {
     case 1: hipLaunchKernelGGL((k_batch_quantize<4, 4, 4, 8, false>), g, b, 0, s, a); break;
@@ -648,13 +647,18 @@ lcq_status lcq_batch_plan_create(const lcq_field *f, uint32_t nf, const char *tu
     const uint64_t ndt = (x.n + kDeqTile - 1) / kDeqTile;
     for (uint64_t t = 0; t < ndt; t++) items_d.push_back(((uint64_t)i << 32) | t);
   }
-  // phase B: larger fields first (their tiles are the long tail), each
-  // field's tiles in increasing order
+  // phase B: fields whose bound needs no range first (they fill the GPU while
+  // the range items still run; a NOA tile dispatched then would only hold
+  // its slot waiting for its field's parameters), then larger fields first
+  // (their tiles are the long tail), each field's tiles in increasing order
   std::vector<uint32_t> order(nf);
   for (uint32_t i = 0; i < nf; i++) order[i] = i;
   std::stable_sort(order.begin(), order.end(),
-                   [&](uint32_t a, uint32_t b) { return f[a].n * (f[a].t == LCQ_F64 ? 8 : 4) >
-                                                        f[b].n * (f[b].t == LCQ_F64 ? 8 : 4); });
+                   [&](uint32_t a, uint32_t b) {
+                     const bool na = f[a].q == LCQ_NOA, nb = f[b].q == LCQ_NOA;
+                     if (na != nb) return nb;
+                     return f[a].n * (f[a].t == LCQ_F64 ? 8 : 4) > f[b].n * (f[b].t == LCQ_F64 ? 8 : 4);
+                   });
   for (uint32_t i : order) {
     for (uint64_t t = 0; t < bf[i].ntiles; t++) items_b.push_back(((uint64_t)i << 32) | t);
   }
@@ -702,13 +706,6 @@ lcq_status lcq_batch_plan_create(const lcq_field *f, uint32_t nf, const char *tu
   da.n_items = c.n_d;
   da.status = reinterpret_cast<unsigned long long *>(ws + L.dstatus);
 
-  if (hipMemcpyAsync(ws + L.args, &qa, sizeof qa, hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess) {
-    delete p;
-    return LCQ_ERR_HIP;
-  }
-  const BatchQArgs *qa_dev = reinterpret_cast<const BatchQArgs *>(ws + L.args);
-
   // capture: clear + quantize; clear + dequantize
   hipStream_t cs;
   if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) { delete p; return LCQ_ERR_HIP; }
@@ -718,9 +715,9 @@ lcq_status lcq_batch_plan_create(const lcq_field *f, uint32_t nf, const char *tu
   if (st == LCQ_OK) {
     hipLaunchKernelGGL(k_batch_clear, dim3(cgrid), dim3(kBlock), 0, cs,
                        reinterpret_cast<uint64_t *>(ws), L.clear_words);
-    if (qa.n_items) st = launch_batch_quantize(bv, qa_dev, p->grid, cs);
+    if (qa.n_items) st = launch_batch_quantize(bv, qa, p->grid, cs);
     if (st == LCQ_OK && kBatchVariants[bv].chunk && c.n_f) {
-      hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)c.n_f), dim3(kBlock), 0, cs, qa_dev);
+      hipLaunchKernelGGL(k_batch_finish, dim3((unsigned)c.n_f), dim3(kBlock), 0, cs, qa);
       if (hipGetLastError() != hipSuccess) st = LCQ_ERR_HIP;
     }
     if (hipStreamEndCapture(cs, &p->gq) != hipSuccess) st = LCQ_ERR_HIP;

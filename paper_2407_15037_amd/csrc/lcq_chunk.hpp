@@ -177,13 +177,32 @@ template <typename T> struct StageField {
   FieldParams<T> p;
 };
 
-// The 16 values per lane of chunk c (zeros past n).
+// The 16 values per lane of chunk c (c uniform; zeros past n).  A full
+// float64 chunk is read from a scalar base with one 32-bit lane offset and
+// constant sub-block offsets: its eight 64-bit addresses and bounds tests
+// cost the registers of a wavefront per SIMD.  float32 has four, keeps all
+// wavefronts either way, and measured faster with the test between its
+// loads (512^3 ABS quantize 189.0 us against 191.9 us).
 template <typename T>
 __device__ __forceinline__ void load_chunk(const T *in, uint64_t n, uint64_t c, int lane,
                                            T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W]) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
+  const T *base = in + c * kChunk;
+  const uint64_t left = n - c * kChunk;
+  if (sizeof(T) == 8 && left >= kChunk) {
+    typedef T nv __attribute__((ext_vector_type(16 / sizeof(T))));
 #pragma unroll
-  for (int j = 0; j < NSUB; j++) load_vals<T, W>(in, chunk_value<W>(c, j, lane), n, x[j]);
+    for (int j = 0; j < NSUB; j++) {
+      const nv v = __builtin_nontemporal_load(
+          reinterpret_cast<const nv *>(base + (unsigned)(64 * W * j) + (unsigned)(W * lane)));
+#pragma unroll
+      for (int e = 0; e < W; e++) x[j][e] = v[e];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NSUB; j++)
+      load_vals<T, W>(base, (unsigned)(64 * W * j) + (unsigned)(W * lane), left, x[j]);
+  }
 }
 
 // Number of set bits of the wavefront mask b in lanes below this one, plus
@@ -211,28 +230,31 @@ __device__ __forceinline__ uint64_t valid_lanes(uint64_t left, int j, int e) {
 // their ranks (running rank = outliers of earlier sub-blocks + set bits of
 // lower lanes); the first stage_cap<T>() then leave in contiguous stores.
 // k: the encoder's operands (enc_consts_pinned: held in vector registers).
-template <typename T, int Q>
-__device__ __forceinline__ unsigned encode_chunk(const StageField<T> &f, uint64_t c, int lane,
-                                                 const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
-                                                 typename FT<T>::U *srow, const EncK<T> &k) {
+// FULL: the chunk has 1024 values (scalar base, no bounds test).
+template <typename T, int Q, bool FULL>
+__device__ __forceinline__ unsigned encode_chunk_at(const StageField<T> &f, uint64_t c, int lane,
+                                                    const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
+                                                    typename FT<T>::U *srow, const EncK<T> &k) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
-  const uint64_t n = f.n;
-  const uint64_t left = n - c * kChunk;
-  const bool full = left >= kChunk;
+  const uint64_t left = FULL ? (uint64_t)kChunk : f.n - c * kChunk;
+  int32_t *codes = f.codes + c * kChunk;
   unsigned cnt = 0;
 #pragma unroll
   for (int j = 0; j < NSUB; j++) {
-    const uint64_t i0 = chunk_value<W>(c, j, lane);
+    const unsigned pos = (unsigned)(64 * W * j) + (unsigned)(W * lane);
     int32_t code[W];
     uint64_t b[W], any = 0;
 #pragma unroll
     for (int e = 0; e < W; e++) {
-      code[e] = encode<T, Q>(x[j][e], f.p, k);
+      // (pinned in the ragged copy: the compiler would otherwise find the two
+      // copies' arithmetic alike and hoist all of it above their branch, every
+      // bin of the chunk live at once: 100 vector registers for float64 REL)
+      code[e] = encode<T, Q>(FULL ? x[j][e] : pin_v(x[j][e]), f.p, k);
       b[e] = __ballot(code[e] == kSent) & valid_lanes<W>(left, j, e);
       any |= b[e];
     }
-    store_codes<W>(f.codes, i0, n, code);
+    store_codes<W, FULL>(codes, pos, left, code);
     if (any) {  // uniform
       unsigned r = cnt;
 #pragma unroll
@@ -242,7 +264,7 @@ __device__ __forceinline__ unsigned encode_chunk(const StageField<T> &f, uint64_
       }
 #pragma unroll
       for (int e = 0; e < W; e++) {
-        const bool mine = full ? code[e] == kSent : ((b[e] >> lane) & 1u) != 0;
+        const bool mine = FULL ? code[e] == kSent : ((b[e] >> lane) & 1u) != 0;
         if (mine) {
           if (r < kCap) srow[r] = to_bits(x[j][e]);
           r++;
@@ -260,6 +282,14 @@ __device__ __forceinline__ unsigned encode_chunk(const StageField<T> &f, uint64_
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // before the next chunk's writes
   if (lane == 0) f.counts[c] = cnt;
   return cnt;
+}
+
+template <typename T, int Q>
+__device__ __forceinline__ unsigned encode_chunk(const StageField<T> &f, uint64_t c, int lane,
+                                                 const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
+                                                 typename FT<T>::U *srow, const EncK<T> &k) {
+  return f.n - c * kChunk >= kChunk ? encode_chunk_at<T, Q, true>(f, c, lane, x, srow, k)
+                                    : encode_chunk_at<T, Q, false>(f, c, lane, x, srow, k);
 }
 
 // Pass 1 for the CPW * stage_waves<T>() chunks of workgroup `tile`, PF chunks per
@@ -303,23 +333,30 @@ __device__ void quant_chunks(const StageField<T> &f, uint64_t tile) {
 // Pass 1 for the cpw * kWaves chunks of workgroup `tile`, cpw given at run
 // time (the batched form, where every workgroup item first loads its
 // field's descriptor): one chunk per wavefront at a time, chunk (tile cpw +
-// r) kWaves + wave in round r.
+// r) kWaves + wave in round r.  The LDS (a stage row per wavefront, and its
+// count) is the caller's: the batched kernel inlines this function once per
+// dtype and quantizer, and arrays declared here would be allocated once for
+// each of those six copies (31 KiB per workgroup: 5 workgroups per CU
+// instead of 8).
 template <typename T, int Q>
-__device__ void quant_chunks_n(const StageField<T> &f, uint64_t tile, unsigned cpw) {
+__device__ void quant_chunks_n(const StageField<T> &f, uint64_t tile, unsigned cpw,
+                               typename FT<T>::U (*s_stage)[stage_cap<T>()], unsigned *s_cnt) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  __shared__ unsigned s_cnt[kWaves];
-  __shared__ typename FT<T>::U s_stage[kWaves][stage_cap<T>()];  // one row per wavefront
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk logic is scalar
   const uint64_t nch = n_chunks(f.n);
   const EncK<T> k = enc_consts_pinned<T, Q>(f.p);
   unsigned wsum = 0;
+#pragma nounroll
   for (unsigned r = 0; r < cpw; r++) {
     const uint64_t c = (tile * cpw + r) * kWaves + wave;
     if (c >= nch) break;  // uniform
+    // (the lane's positions recomputed in every round: hoisted out of the
+    // loop they took the kernel from 36 to 95 vector registers for float32)
+    const int ln = pin_v(lane);
     T x[NSUB][W];
-    load_chunk<T>(f.in, f.n, c, lane, x);
-    wsum += encode_chunk<T, Q>(f, c, lane, x, s_stage[wave], k);
+    load_chunk<T>(f.in, f.n, c, ln, x);
+    wsum += encode_chunk<T, Q>(f, c, ln, x, s_stage[wave], k);
   }
   if (lane == 0) s_cnt[wave] = wsum;
   __syncthreads();
