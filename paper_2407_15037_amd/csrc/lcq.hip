@@ -207,11 +207,10 @@ struct PlainD {
 };
 
 // Header check shared by the dequantize kernels; fills f and returns false
-// (after recording the status) when the stream does not describe this call.
-// `want_q` < 0 accepts the three quantizers, else exactly that (ablation)
-// quantizer code.
+// when the stream does not describe this call.  `want_q` < 0 accepts the
+// three quantizers, else exactly that (ablation) quantizer code.
 template <typename T>
-__device__ __forceinline__ bool deq_setup(const PlainD &a, DField<T> &f, int want_q = -1) {
+__device__ __forceinline__ bool deq_header(const PlainD &a, DField<T> &f, int want_q = -1) {
   using U = typename FT<T>::U;
   const uint64_t n = a.n;
   const uint64_t *hd = reinterpret_cast<const uint64_t *>(a.stream);
@@ -223,10 +222,6 @@ __device__ __forceinline__ bool deq_setup(const PlainD &a, DField<T> &f, int wan
   const bool bad_q = want_q < 0 ? q > 2 : q != want_q;
   const bool bad = (h0 & ~(0xFFull << 48)) != header_word0(a.dtype, 0) || bad_q ||
                    hd[1] != n || k > n || oo + k * sizeof(T) > a.stream_bytes;
-  const unsigned long long tag = (unsigned long long)(a.epoch << 16);
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    report_status(a.status, tag, bad ? LCQ_ERR_STREAM : LCQ_OK);
-  if (bad || n == 0) return false;
   f.stream = a.stream;
   f.n = n;
   f.k = k;
@@ -234,21 +229,47 @@ __device__ __forceinline__ bool deq_setup(const PlainD &a, DField<T> &f, int wan
   f.rel = (q == kREL || q == kREL_LIBM);
   f.out = static_cast<T *>(a.out);
   f.status = a.status;
-  f.tag = tag;
-  return true;
+  f.tag = (unsigned long long)(a.epoch << 16);
+  return !bad;
 }
 
-template <typename T, int CPW, int PF>
-__global__ __launch_bounds__(kBlock) void k_dequantize_chunks(PlainD a) {
+// The same, its verdict recorded first, for the tile kernels.
+template <typename T>
+__device__ __forceinline__ bool deq_setup(const PlainD &a, DField<T> &f) {
+  const bool ok = deq_header<T>(a, f);
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    report_status(f.status, f.tag, ok ? LCQ_OK : LCQ_ERR_STREAM);
+  return ok && a.n != 0;
+}
+
+// One chunk per wavefront.  Every load that does not depend on the header
+// is issued with it, and the call's verdict is recorded after the decode:
+// the reporting thread's two round trips (load, exchange) delay no
+// wavefront's stores.  want_q and LIBM: the section 6 ablation streams.
+template <typename T, bool LIBM>
+__device__ __forceinline__ void deq_chunks(const PlainD &a, int want_q) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar bases
+  const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+  const bool act = c < n_chunks(a.n);
+  DecodeIn<T> d;
+  if (act) load_decode<T>(a.stream, a.n, c, lane, d);
   DField<T> f;
-  if (deq_setup<T>(a, f)) dequant_chunks<T, CPW, PF>(f, blockIdx.x);
+  const bool ok = deq_header<T>(a, f, want_q);
+  if (act && ok) decode_loaded<T, LIBM>(f, c, lane, d);
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    report_status(f.status, f.tag, ok ? LCQ_OK : LCQ_ERR_STREAM);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_dequantize_chunks(PlainD a) {
+  deq_chunks<T, false>(a, -1);
 }
 
 // Decoder of the section 6 ablation streams (quantizer code Q in the header).
 template <typename T, int Q>
 __global__ __launch_bounds__(kBlock) void k_dequantize_ablation(PlainD a) {
-  DField<T> f;
-  if (deq_setup<T>(a, f, Q)) dequant_chunks<T, 1, 1, Q == kREL_LIBM>(f, blockIdx.x);
+  deq_chunks<T, Q == kREL_LIBM>(a, Q);
 }
 
 template <typename T, int SL, int RD>
@@ -334,8 +355,9 @@ template <typename T, int V>
 void launch_dequantize(uint64_t ntiles, const PlainD &a, hipStream_t s) {
   constexpr Shape sh = kDVariants[V];
   if constexpr (sh.cpw > 0) {
-    hipLaunchKernelGGL((k_dequantize_chunks<T, sh.cpw, sh.pf>), dim3((unsigned)ntiles),
-                       dim3(kBlock), 0, s, a);
+    static_assert(sh.cpw == 1, "one chunk per wavefront");
+    hipLaunchKernelGGL(k_dequantize_chunks<T>, dim3((unsigned)ntiles), dim3(kBlock),
+                       lds_for_waves(deq_waves<T>()), s, a);
   } else {
     hipLaunchKernelGGL((k_dequantize<T, sh.slots, sh.rounds>), dim3((unsigned)ntiles),
                        dim3(kBlock), 0, s, a);

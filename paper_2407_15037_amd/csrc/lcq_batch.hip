@@ -367,9 +367,18 @@ struct BatchDArgs {
 };
 
 template <typename T>
-__device__ void deq_item(const BatchDArgs &a, const BField &bf, uint32_t fi, uint64_t tile) {
+__device__ __forceinline__ void deq_item(const BatchDArgs &a, const BField &bf, uint32_t fi,
+                                         uint64_t tile) {
   using U = typename FT<T>::U;
   const uint64_t n = bf.n;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar bases
+  const uint64_t c = tile * kWaves + wave;
+  const bool act = c < n_chunks(n);
+  // codes and chunk-table entries are read together with the header: the
+  // plan checked that the stream buffer holds a whole stream of n values
+  DecodeIn<T> d;
+  if (act) load_decode<T>(bf.stream, n, c, lane, d);
   const uint64_t *hd = reinterpret_cast<const uint64_t *>(bf.stream);
   const uint64_t h0 = hd[0];
   const uint64_t k = hd[2];
@@ -389,7 +398,7 @@ __device__ void deq_item(const BatchDArgs &a, const BField &bf, uint32_t fi, uin
   f.out = static_cast<T *>(bf.out);
   f.status = a.status + fi;
   f.tag = 0;
-  dequant_chunks<T, 1, 1>(f, tile);
+  if (act) decode_loaded<T>(f, c, lane, d);
 }
 
 __global__ __launch_bounds__(kBlock) void k_batch_dequantize(BatchDArgs a) {

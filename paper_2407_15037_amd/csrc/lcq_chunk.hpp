@@ -90,9 +90,10 @@ __device__ __forceinline__ void load_vals(const T *in, uint64_t i0, uint64_t n, 
   }
 }
 
-template <typename T, int W>
+// (FULL: the caller knows all W lie below n)
+template <typename T, int W, bool FULL = false>
 __device__ __forceinline__ void store_vals(T *out, uint64_t i0, uint64_t n, const T (&y)[W]) {
-  if (i0 + W <= n) {
+  if (FULL || i0 + W <= n) {
     if constexpr (sizeof(T) == 4) {
       const nt_f4 o = {y[0], y[1], y[2], y[3]};
       __builtin_nontemporal_store(o, reinterpret_cast<nt_f4 *>(out + i0));
@@ -147,22 +148,6 @@ __device__ __forceinline__ void store_codes(int32_t *codes, uint64_t i0, uint64_
 template <int W>
 __device__ __forceinline__ uint64_t chunk_value(uint64_t c, int j, int lane) {
   return c * kChunk + (uint64_t)(64 * W) * (unsigned)j + (uint64_t)W * (unsigned)lane;
-}
-
-// Ranks of flagged values of one sub-block inside the wavefront's chunk:
-// returns the count of the sub-block to every lane, and in `pre` the number
-// of flagged values of lower lanes.  `fl` holds the lane's W flags.
-template <int W>
-__device__ __forceinline__ unsigned sub_ranks(unsigned fl, uint64_t lt, unsigned &pre) {
-  unsigned tot = 0;
-  pre = 0;
-#pragma unroll
-  for (int e = 0; e < W; e++) {
-    const uint64_t b = __ballot((fl >> e) & 1u);
-    tot += (unsigned)__popcll(b);
-    pre += (unsigned)__popcll(b & lt);
-  }
-  return tot;
 }
 
 // ------------------------------------------------------------- pass 1 ---
@@ -615,116 +600,186 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
 }
 
 // ---------------------------------------------------------- dequantize ---
-// The 16 codes per lane of chunk c (zeros past n).
+// The 16 codes per lane of chunk c (c uniform; zeros past n), from a scalar
+// base (as load_chunk).
 template <int W, int NSUB>
 __device__ __forceinline__ void load_chunk_codes(const int32_t *codes, uint64_t n, uint64_t c,
                                                  int lane, int32_t (&cc)[NSUB][W]) {
-#pragma unroll
-  for (int j = 0; j < NSUB; j++) load_codes<W>(codes, chunk_value<W>(c, j, lane), n, cc[j]);
-}
-
-// Decode chunk c from its codes cc: gather its outliers, check its
-// chunk-table entry, store its values (LIBM: the library-exp2 REL ablation).
-// cur and nxt: the chunk's chunk-table entry and the next one (the
-// outlier count after the last chunk), loaded by the caller; the outliers
-// are at outl (their LCQ1 place for decode_chunk).  REL: the stream's
-// quantizer is REL (a template parameter, so each value's decode is
-// straight-line code and a sentinel's zero one select).
-template <typename T, bool LIBM, bool REL>
-__device__ __forceinline__ void decode_chunk_at(const DField<T> &f, uint64_t cur, uint64_t nxt,
-                                                const typename FT<T>::U *outl, uint64_t c,
-                                                int lane, uint64_t lt,
-                                                const int32_t (&cc)[ChunkShape<T>::NSUB][ChunkShape<T>::W]) {
-  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  constexpr unsigned kLaneMask = (1u << W) - 1;
-  const uint64_t n = f.n;
-  unsigned om = 0;
-  T y[NSUB][W];
-#pragma unroll
-  for (int j = 0; j < NSUB; j++) {
-    const uint64_t i0 = chunk_value<W>(c, j, lane);
-#pragma unroll
-    for (int e = 0; e < W; e++) {
-      const bool sent = cc[j][e] == kSent;
-      const T v = decode<T, LIBM>(cc[j][e], f.step, REL);  // (harmless for a sentinel)
-      y[j][e] = sent ? (T)0 : v;
-      if (sent && i0 + e < n) om |= 1u << (W * j + e);
-    }
-  }
-  uint64_t cnt = 0;
-  if (__ballot(om != 0)) {
+  const int32_t *base = codes + c * kChunk;
+  const uint64_t left = n - c * kChunk;
+  if (left >= kChunk) {
+    typedef int nv __attribute__((ext_vector_type(W)));
 #pragma unroll
     for (int j = 0; j < NSUB; j++) {
-      unsigned pre;
-      const unsigned tot = sub_ranks<W>((om >> (W * j)) & kLaneMask, lt, pre);
-      uint64_t r = cur + cnt + pre;
+      const nv v = __builtin_nontemporal_load(
+          reinterpret_cast<const nv *>(base + (unsigned)(64 * W * j) + (unsigned)(W * lane)));
 #pragma unroll
-      for (int e = 0; e < W; e++) {
-        if ((om >> (W * j + e)) & 1u) {
-          // ranks are checked against the outlier count: never read past it
-          y[j][e] = (r < f.k) ? from_bits(outl[r]) : (T)0;
-          r++;
-        }
-      }
-      cnt += tot;
+      for (int e = 0; e < W; e++) cc[j][e] = v[e];
     }
-  }
-  // the chunk-table entry must count exactly the sentinels before it
-  if (lane == 0 && (cur > f.k || nxt - cur != cnt || (c == 0 && cur != 0)))
-    report_status(f.status, f.tag, LCQ_ERR_STREAM);
+  } else {
 #pragma unroll
-  for (int j = 0; j < NSUB; j++) store_vals<T, W>(f.out, chunk_value<W>(c, j, lane), n, y[j]);
+    for (int j = 0; j < NSUB; j++)
+      load_codes<W>(base, (unsigned)(64 * W * j) + (unsigned)(W * lane), left, cc[j]);
+  }
 }
 
-// decode_chunk_at with the quantizer kind (uniform) made a template
-// parameter.  (Making the chunk's fullness one too -- four inlined copies,
-// 32-bit position tests -- measured slower: 8-16 us on the REL dequantize,
-// 11-47 us on the fused decompress.)
+// The chunk-table entry of chunk c must count exactly the sentinels before it
+// (cnt: those of the chunk).
+template <typename T>
+__device__ __forceinline__ void check_chunk(const DField<T> &f, uint64_t cur, uint64_t nxt,
+                                            unsigned cnt, uint64_t c, int lane) {
+  if (lane == 0 && (cur > f.k || nxt - cur != cnt || (c == 0 && cur != 0)))
+    report_status(f.status, f.tag, LCQ_ERR_STREAM);
+}
+
+// v of lane `src` (mod 64), 32 or 64 bits, through the LDS permute network
+// (no LDS storage).
+__device__ __forceinline__ uint32_t lane_read(uint32_t v, unsigned src) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)v);
+}
+__device__ __forceinline__ uint64_t lane_read(uint64_t v, unsigned src) {
+  return (uint64_t)lane_read((uint32_t)v, src) |
+         ((uint64_t)lane_read((uint32_t)(v >> 32), src) << 32);
+}
+
+// The chunk's outliers as one row over the wavefront: lane l holds outlier l
+// of the first 64 (their index range [cur, nxt) comes from the chunk table,
+// so the row is loaded while the codes are decoded, in one instruction, and
+// costs two registers at most; gathering each value by its rank held the
+// whole chunk's values, 32 registers for float64, across a second round
+// trip).  Never past the outlier count k.
+template <typename T> struct OutlierRow {
+  const typename FT<T>::U *outl;
+  uint64_t cur, k;
+  unsigned have;  // outliers in the row (uniform)
+  typename FT<T>::U row;
+};
+template <typename T>
+__device__ __forceinline__ OutlierRow<T> load_outlier_row(const typename FT<T>::U *outl,
+                                                          uint64_t cur, uint64_t nxt, uint64_t k,
+                                                          int lane) {
+  OutlierRow<T> o;
+  o.outl = outl;
+  o.cur = cur;
+  o.k = k;
+  const uint64_t d = nxt - cur;
+  o.have = d < 64 ? (unsigned)d : 64u;
+  const uint64_t r = cur + (unsigned)lane;
+  o.row = 0;
+  if ((unsigned)lane < o.have && r < k) o.row = outl[r];
+  return o;
+}
+
+// Sub-block j of a chunk: the lane's W codes decoded, sentinels replaced by
+// their outliers (by rank: from the row, or past it from memory), stored.
+// cnt: sentinels of the chunk before this sub-block, advanced.  FULL: the
+// chunk has 1024 values; else `left`.  LIBM: the library-exp2 REL ablation.
+template <typename T, bool LIBM, bool REL, bool FULL>
+__device__ __forceinline__ void decode_sub(const OutlierRow<T> &o, T step, T *out, uint64_t left,
+                                           int j, int lane,
+                                           const int32_t (&cc)[ChunkShape<T>::W], unsigned &cnt) {
+  using U = typename FT<T>::U;
+  constexpr int W = ChunkShape<T>::W;
+  const unsigned pos = (unsigned)(64 * W * j) + (unsigned)(W * lane);
+  T y[W];
+  uint64_t b[W], any = 0;
+#pragma unroll
+  for (int e = 0; e < W; e++) {
+    y[e] = decode<T, LIBM>(cc[e], step, REL);  // (harmless for a sentinel)
+    b[e] = __ballot(cc[e] == kSent) & valid_lanes<W>(FULL ? (uint64_t)kChunk : left, j, e);
+    any |= b[e];
+  }
+  if (any) {  // uniform
+    unsigned r = cnt;
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      r = lanes_below(b[e], r);
+      cnt += (unsigned)__popcll(b[e]);
+    }
+    const bool past = cnt > o.have;  // uniform
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      U v = lane_read(o.row, r);
+      const bool mine = ((b[e] >> lane) & 1u) != 0;
+      if (past && mine && r >= o.have) {
+        const uint64_t i = o.cur + r;  // checked against the outlier count
+        v = i < o.k ? o.outl[i] : (U)0;
+      }
+      y[e] = mine ? from_bits(v) : y[e];
+      r += mine ? 1u : 0u;
+    }
+  }
+  store_vals<T, W, FULL>(out, pos, left, y);
+}
+
+// Decode chunk c from its codes cc: its outliers put in, its chunk-table
+// entry checked, its values stored.  cur and nxt: the chunk's chunk-table
+// entry and the next one (the outlier count after the last chunk), loaded
+// by the caller; the outliers are at outl.  REL: the stream's quantizer is
+// REL (a template parameter, so each value's decode is straight-line code).
+template <typename T, bool LIBM, bool REL, bool FULL>
+__device__ __forceinline__ void decode_chunk_at(const DField<T> &f, const OutlierRow<T> &o,
+                                                uint64_t nxt, uint64_t c, int lane,
+                                                const int32_t (&cc)[ChunkShape<T>::NSUB][ChunkShape<T>::W]) {
+  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
+  const uint64_t left = FULL ? (uint64_t)kChunk : f.n - c * kChunk;
+  T *out = f.out + c * kChunk;
+  unsigned cnt = 0;
+#pragma unroll
+  for (int j = 0; j < NSUB; j++) {
+    // (pinned in the ragged copy: see encode_chunk_at)
+    int32_t code[W];
+#pragma unroll
+    for (int e = 0; e < W; e++) code[e] = FULL ? cc[j][e] : pin_v(cc[j][e]);
+    decode_sub<T, LIBM, REL, FULL>(o, f.step, out, left, j, lane, code, cnt);
+  }
+  check_chunk(f, o.cur, nxt, cnt, c, lane);
+}
+
+// decode_chunk_at with the quantizer kind and the chunk's fullness (both
+// uniform) made template parameters.
 template <typename T, bool LIBM>
 __device__ __forceinline__ void decode_chunk_any(const DField<T> &f, uint64_t cur, uint64_t nxt,
                                                  const typename FT<T>::U *outl, uint64_t c,
-                                                 int lane, uint64_t lt,
+                                                 int lane,
                                                  const int32_t (&cc)[ChunkShape<T>::NSUB][ChunkShape<T>::W]) {
-  if (f.rel) decode_chunk_at<T, LIBM, true>(f, cur, nxt, outl, c, lane, lt, cc);
-  else decode_chunk_at<T, LIBM, false>(f, cur, nxt, outl, c, lane, lt, cc);
-}
-
-template <typename T, bool LIBM>
-__device__ __forceinline__ void decode_chunk(const DField<T> &f, uint64_t c, int lane, uint64_t lt,
-                                             const int32_t (&cc)[ChunkShape<T>::NSUB][ChunkShape<T>::W]) {
-  using U = typename FT<T>::U;
-  const uint64_t *chunk_tab = reinterpret_cast<const uint64_t *>(f.stream + chunk_table_offset(f.n));
-  const U *outl = reinterpret_cast<const U *>(f.stream + outlier_offset(f.n));
-  const uint64_t cur = chunk_tab[c];
-  const uint64_t nxt = (c + 1 < n_chunks(f.n)) ? chunk_tab[c + 1] : f.k;
-  decode_chunk_any<T, LIBM>(f, cur, nxt, outl, c, lane, lt, cc);
-}
-
-// Decode the CPW * kWaves chunks of workgroup `tile`, PF chunks per
-// wavefront loaded at a time.
-template <typename T, int CPW, int PF, bool LIBM = false>
-__device__ void dequant_chunks(const DField<T> &f, uint64_t tile) {
-  static_assert(PF > 0 && CPW % PF == 0, "whole prefetch groups");
-  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t n = f.n;
-  const uint64_t nch = n_chunks(n);
-  const int32_t *codes = reinterpret_cast<const int32_t *>(f.stream + 64);
-  const uint64_t lt = __lanemask_lt();
-#pragma unroll
-  for (int r0 = 0; r0 < CPW; r0 += PF) {
-    int32_t cc[PF][NSUB][W];
-#pragma unroll
-    for (int p = 0; p < PF; p++) {
-      const uint64_t c = (tile * CPW + r0 + p) * kWaves + wave;
-      if (c < nch) load_chunk_codes<W, NSUB>(codes, n, c, lane, cc[p]);
-    }
-#pragma unroll
-    for (int p = 0; p < PF; p++) {
-      const uint64_t c = (tile * CPW + r0 + p) * kWaves + wave;
-      if (c < nch) decode_chunk<T, LIBM>(f, c, lane, lt, cc[p]);  // uniform
-    }
+  const bool full = f.n - c * kChunk >= kChunk;
+  const OutlierRow<T> o = load_outlier_row<T>(outl, cur, nxt, f.k, lane);
+  if (f.rel) {
+    if (full) decode_chunk_at<T, LIBM, true, true>(f, o, nxt, c, lane, cc);
+    else decode_chunk_at<T, LIBM, true, false>(f, o, nxt, c, lane, cc);
+  } else {
+    if (full) decode_chunk_at<T, LIBM, false, true>(f, o, nxt, c, lane, cc);
+    else decode_chunk_at<T, LIBM, false, false>(f, o, nxt, c, lane, cc);
   }
+}
+
+// What one wavefront reads of an LCQ1 stream before anything depends on
+// the header: the codes of its chunk and the two chunk-table entries
+// (nxt of the last chunk is the header's outlier count, set by the caller).
+// All of it lies below outlier_offset(n), which the host checked against
+// the stream's size, so it may be read whatever the header says: the
+// header's round trip overlaps with these loads instead of preceding them.
+template <typename T> struct DecodeIn {
+  int32_t cc[ChunkShape<T>::NSUB][ChunkShape<T>::W];
+  uint64_t cur, nxt;
+};
+template <typename T>
+__device__ __forceinline__ void load_decode(const uint8_t *stream, uint64_t n, uint64_t c, int lane,
+                                            DecodeIn<T> &d) {
+  const uint64_t *chunk_tab = reinterpret_cast<const uint64_t *>(stream + chunk_table_offset(n));
+  load_chunk_codes<ChunkShape<T>::W, ChunkShape<T>::NSUB>(
+      reinterpret_cast<const int32_t *>(stream + 64), n, c, lane, d.cc);
+  d.cur = chunk_tab[c];
+  d.nxt = chunk_tab[c + 1 < n_chunks(n) ? c + 1 : c];
+}
+template <typename T, bool LIBM = false>
+__device__ __forceinline__ void decode_loaded(const DField<T> &f, uint64_t c, int lane,
+                                              const DecodeIn<T> &d) {
+  using U = typename FT<T>::U;
+  const U *outl = reinterpret_cast<const U *>(f.stream + outlier_offset(f.n));
+  const uint64_t nxt = c + 1 < n_chunks(f.n) ? d.nxt : f.k;
+  decode_chunk_any<T, LIBM>(f, d.cur, nxt, outl, c, lane, d.cc);
 }
 
 }  // namespace lcq

@@ -539,6 +539,9 @@ struct DcmpArgs {
   int dtype;
 };
 
+// LDS of one k_decompress workgroup (each wavefront's whole record).
+constexpr unsigned kDecompressLds = kWaves * (kMaxRecord + 4 * kRowPad);
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_decompress(DcmpArgs a) {
   using U = typename FT<T>::U;
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(kBlock) void k_decompress(DcmpArgs a) {
   f.status = a.status;
   f.tag = tag;
   const U *outl = reinterpret_cast<const U *>(a.in + align16(pl + payload));
-  decode_chunk_any<T, false>(f, ct_cur, ct_nxt, outl, c, lane, __lanemask_lt(), cc);
+  decode_chunk_any<T, false>(f, ct_cur, ct_nxt, outl, c, lane, cc);
 }
 
 __global__ void k_clear_cmp(uint64_t *p, uint64_t count) {
@@ -755,7 +758,8 @@ lcq_status lcq_decompress(lcq_dtype t, const void *d_packed, uint64_t packed_byt
   if (t == LCQ_F32)
     hipLaunchKernelGGL(k_decompress<float>, dim3((unsigned)ntiles), dim3(kBlock), 0, stream, a);
   else
-    hipLaunchKernelGGL(k_decompress<double>, dim3((unsigned)ntiles), dim3(kBlock), 0, stream, a);
+    hipLaunchKernelGGL(k_decompress<double>, dim3((unsigned)ntiles), dim3(kBlock),
+                       lds_for_waves(24, kDecompressLds), stream, a);
   return check_launch_cmp();
 }
 

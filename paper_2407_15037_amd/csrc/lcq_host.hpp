@@ -16,6 +16,20 @@
 
 namespace lcq {
 
+// Dynamic LDS that leaves at most `waves` wavefronts (in workgroups of
+// kWaves) on a CU of 160 KiB LDS, the kernel's own static LDS taken off.  The
+// streaming kernels below need fewer wavefronts than their registers would
+// allow: with all 32 resident, more rows of HBM are open at once than it
+// serves well.
+constexpr unsigned lds_for_waves(unsigned waves, unsigned own = 0) {
+  const unsigned share = 163840u / (waves / (unsigned)kWaves) / 1280u * 1280u;
+  return share > own ? share - own : 0u;
+}
+// Wavefronts per CU of the dequantize: 24 for float32 (512^3 REL 174.0 us with
+// all 32, 169.8 with 24, 176.0 with 16), 16 for float64 (384^3 REL 118.4 with
+// all, 116.2 with 24, 112.5 with 16; ABS 114.7, 113.0, 112.7).
+template <typename T> constexpr unsigned deq_waves() { return sizeof(T) == 4 ? 24u : 16u; }
+
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Largest float not above the positive double v (the user's bound rounded
