@@ -130,9 +130,10 @@ struct StageQ {
   uint64_t n;
   uint8_t *stream;
   uint64_t *stream_bytes;
-  uint32_t *counts;
+  uint16_t *counts;
   void *stage;
-  unsigned long long *group;
+  uint32_t *totals;           // one per pass-1 workgroup, or null:
+  unsigned long long *group;  // one per group
   uint64_t tiles_per_group, chunks_per_group, ngroups;
   const DevParams *noa;
   uint64_t step, inv, bound, low;  // ABS / REL parameters (raw bits)
@@ -161,6 +162,7 @@ __global__ __launch_bounds__(64 * stage_waves<T>()) void k_quant_stage(StageQ a)
   f.codes = reinterpret_cast<int32_t *>(a.stream + 64);
   f.counts = a.counts;
   f.stage = static_cast<U *>(a.stage);
+  f.totals = a.totals;
   f.group = a.group;
   f.tiles_per_group = a.tiles_per_group;
   f.p = stage_params<T, Q>(a);
@@ -177,13 +179,45 @@ __global__ __launch_bounds__(kBlock) void k_quant_finish(StageQ a) {
   f.stream_bytes = a.stream_bytes;
   f.counts = a.counts;
   f.stage = static_cast<const U *>(a.stage);
+  f.totals = a.totals;
   f.group = a.group;
+  f.tiles_per_group = a.tiles_per_group;
   f.chunks_per_group = a.chunks_per_group;
   f.ngroups = a.ngroups;
   f.noa = Q == kNOA ? a.noa : nullptr;
 #pragma unroll
   for (int i = 0; i < 8; i++) f.hdr[i] = a.hdr[i];
   quant_finish<T>(f, blockIdx.x);
+}
+
+// A small field in one workgroup and one launch.
+struct SmallQ {
+  const void *in;
+  uint64_t n;
+  uint8_t *stream;
+  uint64_t *stream_bytes;
+  uint64_t step, inv, bound, low;  // ABS / REL parameters (raw bits)
+  uint64_t eb_down;                // NOA
+  uint64_t hdr[8];
+};
+
+template <typename T, int Q, int K>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_quant_small(SmallQ a) {
+  using U = typename FT<T>::U;
+  SmallField<T> f;
+  f.in = static_cast<const T *>(a.in);
+  f.n = a.n;
+  f.stream = a.stream;
+  f.stream_bytes = a.stream_bytes;
+  f.p.step = from_bits((U)a.step);
+  f.p.inv = from_bits((U)a.inv);
+  f.p.bound = from_bits((U)a.bound);
+  f.p.low = from_bits((U)a.low);
+  f.p.lossless_all = 0;
+  f.eb_down = from_bits((U)a.eb_down);
+#pragma unroll
+  for (int i = 0; i < 8; i++) f.hdr[i] = a.hdr[i];
+  quant_small<T, Q, K>(f);
 }
 
 // In-line layout (the paper's own, section 3.1): a pure map per tile.
@@ -299,11 +333,15 @@ __global__ __launch_bounds__(kBlock) void k_dequantize_inline(PlainD a) {
 // ----------------------------------------------------------- host side ---
 // Workspace layout beyond the status word and the NOA parameters:
 //   single-pass variants  one look-back word per tile at kWsState
-//   two-pass variants     group sums at kWsState, chunk counts, staged raw
-//                         bits (stage_cap<T>() per chunk)
+//   two-pass variants     group sums at kWsState, chunk counts (2 bytes each)
+//                         and pass-1 workgroups' totals in 4 bytes per chunk,
+//                         staged raw bits (stage_cap<T>() per chunk)
 //   NOA                   per-workgroup (min, max) pairs after both
 uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
 uint64_t ws_counts_off() { return align256(kWsState + 8 * kMaxGroups); }
+uint64_t ws_totals_off(uint64_t n) { return align16(ws_counts_off() + 2 * n_chunks(n)); }
+// (2 bytes per chunk, aligned to 16, and 4 per at least 4 chunks: within the
+// 4 per chunk, aligned to 256, for any number of chunks)
 uint64_t ws_stage_off(uint64_t n) { return align256(ws_counts_off() + 4 * n_chunks(n)); }
 uint64_t ws_partials_off(lcq_dtype t, uint64_t n) {
   const uint64_t s = t == LCQ_F64 ? 8 : 4;
@@ -386,6 +424,22 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
   const int v = Q >= kABS_UNCHECKED ? kAblationVariant
                                     : g_variant[0][dt].load(std::memory_order_relaxed);
   const HostParams hp = host_params<T>(Q, eb);
+  if constexpr (Q <= kNOA) {
+    if (n && kQVariants[v].cpw > 0 && n_chunks(n) <= small_chunks<T, Q>()) {
+      SmallQ a{d_in, n, static_cast<uint8_t *>(d_stream), d_bytes,
+               hp.step, hp.inv, hp.bound, hp.low, hp.eb_down,
+               {header_word0(dt, Q), n, 0, __builtin_bit_cast(uint64_t, eb), hp.step, hp.bound,
+                hp.aux0, hp.aux1}};
+      if (g_ev_before) (void)hipEventRecord(g_ev_before, s);
+      if (n_chunks(n) <= kSmallWaves)
+        hipLaunchKernelGGL((k_quant_small<T, Q, 1>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+      else
+        hipLaunchKernelGGL((k_quant_small<T, Q, kSmallK>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+      if (g_ev_mid) (void)hipEventRecord(g_ev_mid, s);
+      if (g_ev_after) (void)hipEventRecord(g_ev_after, s);
+      return check_launch();
+    }
+  }
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
   PlainQ a{};
   a.in = d_in;
@@ -420,10 +474,14 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
     sq.n = n;
     sq.stream = a.stream;
     sq.stream_bytes = d_bytes;
-    sq.counts = reinterpret_cast<uint32_t *>(ws + ws_counts_off());
+    sq.counts = reinterpret_cast<uint16_t *>(ws + ws_counts_off());
     sq.stage = ws + ws_stage_off(n);
     sq.group = reinterpret_cast<unsigned long long *>(ws + kWsState);
-    sq.tiles_per_group = tiles_per_group(a.ntiles, tile / kChunk);
+    sq.tiles_per_group = tiles_per_group(a.ntiles, tile / kChunk, kGroupChunksAlone);
+    if (a.ntiles <= kMaxDirectTiles) {
+      sq.totals = reinterpret_cast<uint32_t *>(ws + ws_totals_off(n));
+      sq.tiles_per_group = (sq.tiles_per_group + 3) / 4 * 4;  // read four at a time
+    }
     sq.chunks_per_group = sq.tiles_per_group * (tile / kChunk);
     sq.ngroups = (a.ntiles + sq.tiles_per_group - 1) / sq.tiles_per_group;
     sq.noa = a.noa;
@@ -433,7 +491,7 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
     sq.low = a.low;
     for (int i = 0; i < 8; i++) sq.hdr[i] = a.hdr[i];
     clear_ptr = reinterpret_cast<uint64_t *>(sq.group);
-    clear_count = sq.ngroups;
+    clear_count = sq.totals ? 0 : sq.ngroups;
   }
 
   if (Q == kNOA) {

@@ -275,8 +275,9 @@ __device__ __forceinline__ void chunk_item(const BatchQArgs &a, const BField &bf
   f.in = static_cast<const T *>(bf.in);
   f.n = bf.n;
   f.codes = reinterpret_cast<int32_t *>(bf.stream + 64);
-  f.counts = reinterpret_cast<uint32_t *>(a.ws + bf.counts_off);
+  f.counts = reinterpret_cast<uint16_t *>(a.ws + bf.counts_off);
   f.stage = reinterpret_cast<U *>(a.ws + bf.stage_off);
+  f.totals = nullptr;
   f.group = reinterpret_cast<unsigned long long *>(a.ws + bf.group_off);
   f.tiles_per_group = bf.tiles_per_group;
   f.p = field_params<T, Q>(a, bf, nullptr);
@@ -340,9 +341,11 @@ __device__ __forceinline__ void finish_item(const BatchQArgs &a, const BField &b
   f.n = bf.n;
   f.stream = bf.stream;
   f.stream_bytes = bf.stream_bytes;
-  f.counts = reinterpret_cast<const uint32_t *>(a.ws + bf.counts_off);
+  f.counts = reinterpret_cast<const uint16_t *>(a.ws + bf.counts_off);
   f.stage = reinterpret_cast<const U *>(a.ws + bf.stage_off);
+  f.totals = nullptr;
   f.group = reinterpret_cast<const unsigned long long *>(a.ws + bf.group_off);
+  f.tiles_per_group = bf.tiles_per_group;
   f.chunks_per_group = bf.chunks_per_group;
   f.ngroups = bf.ngroups;
   f.noa = bf.q == kNOA ? a.params + bf.noa_idx : nullptr;
@@ -463,7 +466,7 @@ Counts count(const lcq_field *f, uint32_t nf, const Tune &tn) {
       field_groups(nt, tn.cpw(f[i].t), tpg, ng);
       c.n_f += ng;
       c.group_words += ng;
-      c.count_bytes += up256(4 * n_chunks(f[i].n));
+      c.count_bytes += up256(2 * n_chunks(f[i].n));
       c.stage_bytes += up256(stage_bytes_per_chunk(f[i].t) * n_chunks(f[i].n));
     } else {
       c.states += nt;
@@ -639,7 +642,7 @@ lcq_status lcq_batch_plan_create(const lcq_field *f, uint32_t nf, const char *tu
       d.counts_off = L.counts + count_off;
       d.stage_off = L.stage + stage_off;
       group_off += d.ngroups;
-      count_off += up256(4 * n_chunks(x.n));
+      count_off += up256(2 * n_chunks(x.n));
       stage_off += up256(stage_bytes_per_chunk(x.t) * n_chunks(x.n));
       for (uint64_t g = 0; g < d.ngroups; g++) items_f.push_back(((uint64_t)i << 32) | g);
     } else {

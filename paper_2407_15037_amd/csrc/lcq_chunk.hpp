@@ -13,8 +13,8 @@
 //   pass 1  per value classify / bin / reconstruct / verify (sections 2.2,
 //           3.1-3.3), int32 code stores, the chunk's outlier count, and the
 //           first stage_cap<T>() outliers' raw bits staged per chunk; one
-//           atomic add per workgroup into the sum of its group of
-//           workgroups.
+//           count per workgroup (very large fields: one atomic add into the
+//           sum of its group of workgroups).
 //   pass 2  one workgroup per group: exclusive scan of the chunk counts
 //           (the chunk table), copy of staged outliers to their final,
 //           input-ordered place, header and size.  A chunk with more than
@@ -47,19 +47,28 @@ typedef int nt_i2 __attribute__((ext_vector_type(2)));
 // the cap is rescanned from its codes and input in pass 2, at the cost of
 // reading both again.
 template <typename T> constexpr int stage_cap() { return sizeof(T) == 4 ? 128 : 256; }
-// Pass 2 copies the staged rows of chunks with at most kDirect outliers in
-// the chunk's own group; rows of chunks with more (hard stretches of data
-// come in runs) are spread over every pass-2 workgroup, as are the rescans.
-constexpr int kDirect = 32;
 constexpr uint64_t kMaxGroups = 1024;  // pass-2 workgroups (groups) at most
-constexpr uint64_t kGroupChunks = 64;  // chunks per group at least
+constexpr uint64_t kGroupChunks = 64;  // chunks per group at least (many fields at once)
+// The same for one field alone, which has no other field's groups to fill
+// the GPU with: a 3 M value float32 REL field at 1e-5, whose chunks mostly
+// exceed the stage cap, kept 46 workgroups of 64 rescans each busy for 18 us.
+constexpr uint64_t kGroupChunksAlone = 16;
+// Up to this many pass-1 workgroups each stores its own outlier count and
+// pass 2 sums those of the earlier groups itself (8 KiB at most, two loads
+// per thread); above it the counts go to one atomic sum per group, which a
+// kernel of its own has to clear first.  The launch saved is a third of a
+// small field's; a large one does not show it (the clear runs in the shadow
+// of the operation before), and 16,384 totals summed by each of 1024 pass-2
+// workgroups cost more than the clear (512^3 float32 ABS 195 us against 191).
+constexpr uint64_t kMaxDirectTiles = 2048;
 
 // Pass-1 workgroups per pass-2 group for a field of `ntiles` pass-1
-// workgroups of `chunks_per_tile` chunks each: at least kGroupChunks chunks
+// workgroups of `chunks_per_tile` chunks each: at least min_chunks chunks
 // per group (fewer, fuller pass-2 workgroups for many small fields), at
 // most kMaxGroups groups.
-__host__ __device__ inline uint64_t tiles_per_group(uint64_t ntiles, uint64_t chunks_per_tile) {
-  const uint64_t by_size = (kGroupChunks + chunks_per_tile - 1) / chunks_per_tile;
+__host__ __device__ inline uint64_t tiles_per_group(uint64_t ntiles, uint64_t chunks_per_tile,
+                                                    uint64_t min_chunks = kGroupChunks) {
+  const uint64_t by_size = (min_chunks + chunks_per_tile - 1) / chunks_per_tile;
   const uint64_t by_count = (ntiles + kMaxGroups - 1) / kMaxGroups;
   return by_size > by_count ? by_size : by_count;
 }
@@ -155,8 +164,9 @@ template <typename T> struct StageField {
   const T *in;
   uint64_t n;
   int32_t *codes;                 // stream + 64
-  uint32_t *counts;               // one per chunk
+  uint16_t *counts;               // one per chunk (at most 1024)
   typename FT<T>::U *stage;       // stage_cap<T>() per chunk
+  uint32_t *totals;               // one count per workgroup, or null:
   unsigned long long *group;      // one sum per group of workgroups
   uint64_t tiles_per_group;
   FieldParams<T> p;
@@ -265,7 +275,7 @@ __device__ __forceinline__ unsigned encode_chunk_at(const StageField<T> &f, uint
   for (unsigned b = 0; b < staged; b += 64)
     if (b + (unsigned)lane < staged) f.stage[c * kCap + b + lane] = srow[b + lane];
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // before the next chunk's writes
-  if (lane == 0) f.counts[c] = cnt;
+  if (lane == 0) f.counts[c] = (uint16_t)cnt;
   return cnt;
 }
 
@@ -308,10 +318,11 @@ __device__ void quant_chunks(const StageField<T> &f, uint64_t tile) {
   if (lane == 0) s_cnt[wave] = wsum;
   __syncthreads();
   if (tid == 0) {
-    unsigned long long t = 0;
+    unsigned t = 0;
 #pragma unroll
     for (int w = 0; w < kSW; w++) t += s_cnt[w];
-    if (t) atomicAdd(f.group + tile / f.tiles_per_group, t);
+    if (f.totals) f.totals[tile] = t;
+    else if (t) atomicAdd(f.group + tile / f.tiles_per_group, (unsigned long long)t);
   }
 }
 
@@ -353,15 +364,45 @@ __device__ void quant_chunks_n(const StageField<T> &f, uint64_t tile, unsigned c
   }
 }
 
+// Header (outlier count k; NOA: the device's parameters), padding and size
+// of an LCQ1 stream, by one thread.
+template <typename T>
+__device__ __forceinline__ void finish_stream(uint8_t *stream, uint64_t *stream_bytes, uint64_t n,
+                                              const uint64_t (&hdr)[8], uint64_t k,
+                                              const DevParams *noa) {
+  const uint64_t nch = n_chunks(n);
+  const uint64_t ct = chunk_table_offset(n);
+  const uint64_t ce = ct + 8 * nch;
+  const uint64_t oo = outlier_offset(n);
+  for (uint64_t x = 64 + 4 * n; x < ct; x++) stream[x] = 0;
+  for (uint64_t x = ce; x < oo; x++) stream[x] = 0;
+  uint64_t h[8];
+#pragma unroll
+  for (int i = 0; i < 8; i++) h[i] = hdr[i];
+  h[2] = k;
+  if (noa) {
+    h[4] = noa->step;
+    h[5] = noa->bound;
+    h[6] = noa->lo;
+    h[7] = noa->hi;
+  }
+  uint64_t *hd = reinterpret_cast<uint64_t *>(stream);
+#pragma unroll
+  for (int i = 0; i < 8; i++) hd[i] = h[i];
+  *stream_bytes = oo + k * sizeof(T);
+}
+
 // ------------------------------------------------------------- pass 2 ---
 template <typename T> struct FinishField {
   const T *in;
   uint64_t n;
   uint8_t *stream;
   uint64_t *stream_bytes;
-  const uint32_t *counts;
+  const uint16_t *counts;
   const typename FT<T>::U *stage;
+  const uint32_t *totals;  // pass-1 workgroups' counts, or null:
   const unsigned long long *group;
+  uint64_t tiles_per_group;  // (with totals: a multiple of 4)
   uint64_t chunks_per_group;
   uint64_t ngroups;
   const DevParams *noa;  // NOA: header words 4-7 come from here
@@ -399,40 +440,66 @@ __device__ void rescan_chunk(const FinishField<T> &f, typename FT<T>::U *outl, u
   }
 }
 
-// The staged row of chunk c (cnt <= stage cap outliers) to outl from index
-// P on.  One wavefront; every load is issued before the first store.
+// The staged rows of a pass-2 workgroup's chunks to their places, one
+// outlier per thread: outlier t of the batch's `total` belongs to the chunk i
+// with s_P[i] <= t < s_P[i + 1] (found by bisection of the kBlock prefixes in
+// LDS; chunks past the batch's end hold `total`) and is entry t - s_P[i] of
+// its row.  Outliers of chunks over the stage cap are left out.  Reads follow
+// the rows, writes are contiguous, a batch without outliers costs nothing,
+// and the work is spread evenly whatever the counts: chunk by chunk, with
+// rows of more than 32 taken by one wavefront after another, this took 24 of
+// the 29 us of pass 2 for a 3 M value float32 REL field at 1e-5 (about 100
+// outliers in every chunk).  Short loops on purpose: unrolled over 16 rows
+// the kernel's instruction fetch cost more than the loads it overlapped.
 template <typename T>
-__device__ __forceinline__ void copy_staged(const FinishField<T> &f, typename FT<T>::U *outl,
-                                            uint64_t c, uint64_t P, unsigned cnt, int lane) {
+__device__ __forceinline__ void copy_rows(const typename FT<T>::U *stage, typename FT<T>::U *out,
+                                          const unsigned *s_P, const unsigned *s_c,
+                                          unsigned total) {
   using U = typename FT<T>::U;
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
-  constexpr int kR = (int)kCap / 64;
-  U v[kR];
+  constexpr int kRound = 4;  // outliers per thread in flight
+#pragma nounroll
+  for (unsigned t0 = threadIdx.x; t0 < total; t0 += kBlock * kRound) {
+    unsigned i[kRound], t[kRound];
 #pragma unroll
-  for (int r = 0; r < kR; r++) {
-    const unsigned i = (unsigned)lane + 64u * r;
-    if (i < cnt) v[r] = f.stage[c * kCap + i];
-  }
+    for (int u = 0; u < kRound; u++) {
+      t[u] = min(t0 + (unsigned)(u * kBlock), total - 1);
+      i[u] = 0;
+    }
+#pragma nounroll
+    for (unsigned step = kBlock / 2; step; step >>= 1) {
 #pragma unroll
-  for (int r = 0; r < kR; r++) {
-    const unsigned i = (unsigned)lane + 64u * r;
-    if (i < cnt) outl[P + i] = v[r];
+      for (int u = 0; u < kRound; u++) i[u] += s_P[i[u] + step] <= t[u] ? step : 0u;
+    }
+    U v[kRound];
+    unsigned ok = 0;
+#pragma unroll
+    for (int u = 0; u < kRound; u++) {
+      // (an outlier not staged reads some word of its chunk's row)
+      const unsigned r = min(t[u] - s_P[i[u]], kCap - 1);
+      v[u] = stage[i[u] * kCap + r];
+      ok |= (s_c[i[u]] <= kCap && t0 + (unsigned)(u * kBlock) < total ? 1u : 0u) << u;
+    }
+#pragma unroll
+    for (int u = 0; u < kRound; u++)
+      if ((ok >> u) & 1u) out[t[u]] = v[u];
   }
 }
 
 static_assert(LCQ_MAX_N / kChunk <= 0xFFFFFFFFull, "chunk indices fit 32 bits");
 
-// Index of chunk c's first outlier, from the pass-1 group sums and chunk
-// counts alone (so any workgroup can find it before the chunk table is
-// written).  One wavefront; uniform result.
+// Index of chunk c's first outlier, from the pass-1 group sums (with totals:
+// their prefix in s_grp) and chunk counts alone (so any workgroup can find
+// it before the chunk table is written).  One wavefront; uniform result.
 template <typename T>
-__device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int lane) {
+__device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int lane,
+                                        const unsigned *s_grp) {
   // chunk and group indices fit 32 bits (n <= LCQ_MAX_N = 2^38)
   const uint64_t gc = (uint32_t)c / (uint32_t)f.chunks_per_group;
   unsigned long long s = 0;
   // eight loads per lane in flight per round (unconditional loads at a
   // clamped index, masked afterwards)
-  for (uint64_t i0 = (uint64_t)lane; i0 < gc; i0 += 64 * 8) {
+  for (uint64_t i0 = (uint64_t)lane; !f.totals && i0 < gc; i0 += 64 * 8) {
 #pragma unroll
     for (int k = 0; k < 8; k++) {
       const uint64_t i = i0 + 64 * (uint64_t)k;
@@ -448,7 +515,46 @@ __device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int
       s += i < c ? v : 0u;
     }
   }
-  return wave_sum(s);
+  return wave_sum(s) + (f.totals ? s_grp[gc] : 0u);
+}
+
+// Exclusive prefix of the groups' outlier counts, from the pass-1 workgroups'
+// totals: s_grp[g] = outliers of all groups before g, for ngroups groups.
+// One workgroup; ends with a barrier.  (The totals, and so every prefix, fit
+// 32 bits: kMaxDirectTiles workgroups of at most 8192 values.)
+template <typename T>
+__device__ void group_prefix(const FinishField<T> &f, unsigned *s_grp, unsigned *s_wt) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kPer = (int)(kMaxGroups / kBlock);  // consecutive groups per thread
+  const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
+  const unsigned quads = (unsigned)(f.tiles_per_group / 4);
+  unsigned v[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; i++) {
+    const unsigned g = (unsigned)(tid * kPer + i);
+    // (whole groups only; nothing follows the last one)
+    const unsigned m = g + 1 < f.ngroups ? quads : 0u;
+    unsigned t = 0;
+    for (unsigned q0 = 0; q0 < m; q0 += 4) {  // four loads in flight, clamped and masked
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const nt_i4 x = tot[g * quads + (q0 + u < m ? q0 + u : 0)];
+        const unsigned y = (unsigned)x.x + (unsigned)x.y + (unsigned)x.z + (unsigned)x.w;
+        t += q0 + u < m ? y : 0u;
+      }
+    }
+    v[i] = sum;
+    sum += t;
+  }
+  const unsigned incl = wave_incl_add(sum);
+  __syncthreads();  // s_wt's readers before
+  if (lane == 63) s_wt[wave] = incl;
+  __syncthreads();
+  unsigned base = incl - sum;
+  for (int w = 0; w < wave; w++) base += s_wt[w];
+#pragma unroll
+  for (int i = 0; i < kPer; i++) s_grp[tid * kPer + i] = base + v[i];
+  __syncthreads();
 }
 
 // Pass 2 for group g: chunk-table entries of its chunks, their outliers,
@@ -458,10 +564,12 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   using U = typename FT<T>::U;
   __shared__ unsigned long long s_red[kWaves];
   __shared__ unsigned s_wt[kWaves];
-  __shared__ uint64_t s_P[kBlock];
+  __shared__ unsigned s_P[kBlock];
   __shared__ unsigned s_c[kBlock];
+  __shared__ unsigned s_grp[kMaxGroups];
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t n = f.n;
   const uint64_t nch = n_chunks(n);
   uint64_t *chunk_tab = reinterpret_cast<uint64_t *>(f.stream + chunk_table_offset(n));
@@ -479,11 +587,26 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   // (unconditional loads at a clamped index, masked afterwards)
   static_assert(kMaxGroups % kBlock == 0, "whole rounds of group sums");
   unsigned long long b = 0;
+  if (f.totals) {
+    const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
+    const unsigned m = (unsigned)(g * f.tiles_per_group / 4);
+    unsigned t = 0;
+    static_assert(kMaxDirectTiles == 8 * kBlock, "two loads of four per thread");
 #pragma unroll
-  for (int k = 0; k < (int)(kMaxGroups / kBlock); k++) {
-    const uint64_t i = (uint64_t)tid + (uint64_t)k * kBlock;
-    const unsigned long long v = f.group[i < g ? i : 0];
-    b += i < g ? v : 0ull;
+    for (int k = 0; k < 2; k++) {
+      const unsigned i = (unsigned)(tid + k * kBlock);
+      const nt_i4 v = tot[i < m ? i : 0];
+      const unsigned q = (unsigned)v.x + (unsigned)v.y + (unsigned)v.z + (unsigned)v.w;
+      t += i < m ? q : 0u;
+    }
+    b = t;
+  } else {
+#pragma unroll
+    for (int k = 0; k < (int)(kMaxGroups / kBlock); k++) {
+      const uint64_t i = (uint64_t)tid + (uint64_t)k * kBlock;
+      const unsigned long long v = f.group[i < g ? i : 0];
+      b += i < g ? v : 0ull;
+    }
   }
   b = wave_sum(b);
   if (lane == 0) s_red[wave] = b;
@@ -507,50 +630,29 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     }
     const uint64_t P = run + before + (incl - cnt);
     if (c < c1) chunk_tab[c] = P;
-    s_P[tid] = before + (incl - cnt);  // batch-relative first outlier of each chunk
-    s_c[tid] = cnt;                    // (read after the barrier below)
-    const int m = (int)min<uint64_t>((uint64_t)kBlock, c1 - cb);
+    s_P[tid] = (unsigned)before + (incl - cnt);  // batch-relative first outlier of each chunk
+    s_c[tid] = cnt;                              // (read after the barrier below)
     __syncthreads();  // s_P and s_c whole
-    // staged outliers of chunks with at most kDirect of them: half a
-    // wavefront per chunk, word r of a row moved by lane r of the half (one
-    // row read and one contiguous run written per instruction); the loads
-    // of a round are all issued before its stores
-    {
-      constexpr int kHalves = kBlock / kDirect, kRound = 16;
-      static_assert(kDirect == 32, "a directly copied row is one half wavefront");
-      const int h = tid / kDirect, r = tid % kDirect;
-      for (int i0 = h; i0 < m; i0 += kHalves * kRound) {
-        U v[kRound];
-        uint64_t dst[kRound];
-        bool mv[kRound];
-#pragma unroll
-        for (int u = 0; u < kRound; u++) {
-          const int i = i0 + u * kHalves;
-          const unsigned ci = i < m ? s_c[i] : 0u;
-          mv[u] = ci <= (unsigned)kDirect && (unsigned)r < ci;
-          dst[u] = mv[u] ? run + s_P[i] + (unsigned)r : 0;
-          if (mv[u]) v[u] = f.stage[(cb + (uint64_t)i) * kCap + r];
-        }
-#pragma unroll
-        for (int u = 0; u < kRound; u++)
-          if (mv[u]) outl[dst[u]] = v[u];
-      }
-    }
+    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
     run += total;
     __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
   }
 
-  // Chunks with more than kDirect outliers are finished not by their own
-  // group: workgroup g takes chunks g, g + ngroups, g + 2 ngroups, ... so
+  // Chunks with more outliers than were staged are finished not by their
+  // own group: workgroup g takes chunks g, g + ngroups, g + 2 ngroups, ... so
   // that runs of such chunks (a stretch of hard data) spread over every
-  // workgroup instead of queueing behind one.  One wavefront per such
-  // chunk: its staged row is copied, or, past the stage cap, its outliers
-  // are rescanned from its codes and input.
+  // workgroup instead of queueing behind one.  One wavefront per such chunk
+  // finds its outliers again from its codes and input.
+  bool have_grp = false;
   for (uint64_t t0 = 0; g + t0 * f.ngroups < nch; t0 += kBlock) {
     const uint64_t c = g + (t0 + (uint64_t)tid) * f.ngroups;
     const unsigned cn = t0 == 0 ? duty0 : (c < nch ? f.counts[c] : 0u);
-    const bool ov = cn > (unsigned)kDirect;
+    const bool ov = cn > kCap;
     if (!__syncthreads_or(ov)) continue;
+    if (f.totals && !have_grp) {  // uniform
+      group_prefix<T>(f, s_grp, s_wt);
+      have_grp = true;
+    }
     const uint64_t wb = __ballot(ov);
     if (lane == 0) s_wt[wave] = (unsigned)__popcll(wb);
     __syncthreads();
@@ -560,43 +662,179 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
       if (w < wave) base += s_wt[w];
       nov += s_wt[w];
     }
-    if (ov) {  // compact list of this batch's chunks and their counts
-      s_P[base + lanes_below(wb, 0u)] = c;
-      s_c[base + lanes_below(wb, 0u)] = cn;
-    }
+    if (ov) s_P[base + lanes_below(wb, 0u)] = (unsigned)c;  // compact list of this batch's chunks
     __syncthreads();
     for (unsigned i = (unsigned)wave; i < nov; i += kWaves) {
       const uint64_t cv = s_P[i];
-      const unsigned cc = s_c[i];
-      const uint64_t P = chunk_first_outlier<T>(f, cv, lane);
-      if (cc <= kCap) copy_staged<T>(f, outl, cv, P, cc, lane);
-      else rescan_chunk<T>(f, outl, cv, P, lane);
+      const int ln = pin_v(lane);  // (positions recomputed, not held for the whole kernel)
+      rescan_chunk<T>(f, outl, cv, chunk_first_outlier<T>(f, cv, ln, s_grp), ln);
     }
     __syncthreads();  // s_wt, s_P and s_c are rewritten by the next batch
   }
 
-  if (g == f.ngroups - 1 && tid == 0) {
-    const uint64_t k = run;
-    const uint64_t ct = chunk_table_offset(n);
-    const uint64_t ce = ct + 8 * nch;
-    const uint64_t oo = outlier_offset(n);
-    for (uint64_t x = 64 + 4 * n; x < ct; x++) f.stream[x] = 0;
-    for (uint64_t x = ce; x < oo; x++) f.stream[x] = 0;
-    uint64_t h[8];
+  if (g == f.ngroups - 1 && tid == 0)
+    finish_stream<T>(f.stream, f.stream_bytes, n, f.hdr, run, f.noa);
+}
+
+// ------------------------------------------------- small fields ---
+// A field of at most small_chunks<T, Q>() chunks is quantized by one workgroup of
+// kSmallWaves wavefronts in one launch: range (NOA), codes, chunk table,
+// outliers and header.  At these sizes the launches are the cost, not the
+// bytes: three (NOA: four) dependent launches took 14-16 us of host time
+// for a field one workgroup streams in a few.  Every value stays in
+// registers from its load to the outlier store (K chunks per wavefront),
+// so nothing is staged and the input is read once, NOA's too.
+constexpr int kSmallWaves = 16;
+constexpr int kSmallK = 2;  // chunks per wavefront at most
+// Chunks up to which one workgroup is the faster way (kernel durations: the
+// two passes take 9-10 us together at these sizes, float64 REL 10.4, NOA's
+// four kernels 15.3; one workgroup takes, at 16 and 32 chunks, 5.0 and 8.3 us
+// for float32 ABS, 6.4 and 11.2 REL, 7.2 and 11.6 NOA; float64 5.8 and 10.0
+// ABS, 8.2 and 15.1 REL, 8.2 and 13.5 NOA).
+template <typename T, int Q> constexpr uint64_t small_chunks() {
+  return Q == kNOA || (sizeof(T) == 4 && Q == kABS) ? 32 : sizeof(T) == 4 || Q == kABS ? 24 : 18;
+}
+
+// Finite minimum and maximum of the chunk's values below len (section 2.1.3;
+// -0 counts as +0).
+template <typename T>
+__device__ __forceinline__ void chunk_range(const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
+                                            unsigned len, int lane, T &lo, T &hi) {
+  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
+  using F = FT<T>;
 #pragma unroll
-    for (int i = 0; i < 8; i++) h[i] = f.hdr[i];
-    h[2] = k;
-    if (f.noa) {
-      h[4] = f.noa->step;
-      h[5] = f.noa->bound;
-      h[6] = f.noa->lo;
-      h[7] = f.noa->hi;
+  for (int j = 0; j < NSUB; j++)
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      const T v = x[j][e];
+      const bool in = (unsigned)(64 * W * j + W * lane + e) < len &&
+                      ((to_bits(v) >> F::kMant) & F::kExpMask) != F::kExpMask;
+      const T y = (v == (T)0) ? (T)0 : v;
+      lo = in ? fmin(lo, y) : lo;
+      hi = in ? fmax(hi, y) : hi;
     }
-    uint64_t *hd = reinterpret_cast<uint64_t *>(f.stream);
+}
+
+// Minimum and maximum over a workgroup of WAVES wavefronts, to every thread
+// (s_lo, s_hi: one entry per wavefront).
+template <typename T, int WAVES>
+__device__ __forceinline__ void block_range(T &lo, T &hi, T *s_lo, T *s_hi) {
 #pragma unroll
-    for (int i = 0; i < 8; i++) hd[i] = h[i];
-    *f.stream_bytes = oo + k * sizeof(T);
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o, 64));
+    hi = fmax(hi, __shfl_xor(hi, o, 64));
   }
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    s_lo[wave] = lo;
+    s_hi[wave] = hi;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; w++) {
+    lo = fmin(lo, s_lo[w]);
+    hi = fmax(hi, s_hi[w]);
+  }
+}
+
+template <typename T> struct SmallField {
+  const T *in;
+  uint64_t n;  // 0 < n <= kSmallWaves * K * kChunk
+  uint8_t *stream;
+  uint64_t *stream_bytes;
+  FieldParams<T> p;  // ABS / REL
+  T eb_down;         // NOA
+  uint64_t hdr[8];
+};
+
+template <typename T, int Q, int K>
+__device__ __forceinline__ void quant_small(const SmallField<T> &f) {
+  using U = typename FT<T>::U;
+  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
+  __shared__ T s_lo[kSmallWaves], s_hi[kSmallWaves];
+  __shared__ unsigned s_cnt[64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t n = f.n;
+  const unsigned nch = (unsigned)n_chunks(n);
+  if (tid < 64) s_cnt[tid] = 0;
+  T x[K][NSUB][W];
+#pragma unroll
+  for (int r = 0; r < K; r++) {
+    const unsigned c = (unsigned)(r * kSmallWaves + wave);
+    if (c < nch) load_chunk<T>(f.in, n, c, lane, x[r]);
+  }
+  FieldParams<T> p = f.p;
+  DevParams d;
+  if constexpr (Q == kNOA) {
+    T lo = (T)INFINITY, hi = (T)-INFINITY;
+#pragma unroll
+    for (int r = 0; r < K; r++) {
+      const unsigned c = (unsigned)(r * kSmallWaves + wave);
+      if (c < nch) {
+        const uint64_t left = n - (uint64_t)c * kChunk;
+        chunk_range<T>(x[r], left < kChunk ? (unsigned)left : kChunk, lane, lo, hi);
+      }
+    }
+    block_range<T, kSmallWaves>(lo, hi, s_lo, s_hi);
+    d = noa_params<T>(lo, hi, f.eb_down);
+    p = params_from<T>(d);
+  } else {
+    __syncthreads();  // s_cnt is zero
+  }
+  const EncK<T> k = enc_consts_pinned<T, Q>(p);
+  int32_t *codes = reinterpret_cast<int32_t *>(f.stream + 64);
+  unsigned flags[K];  // bit W j + e: the lane's value of sub-block j is an outlier
+#pragma unroll
+  for (int r = 0; r < K; r++) {
+    const unsigned c = (unsigned)(r * kSmallWaves + wave);
+    flags[r] = 0;
+    if (c >= nch) continue;  // uniform
+    const uint64_t left = n - (uint64_t)c * kChunk;
+    unsigned cnt = 0;
+#pragma unroll
+    for (int j = 0; j < NSUB; j++) {
+      int32_t code[W];
+#pragma unroll
+      for (int e = 0; e < W; e++) {
+        code[e] = encode<T, Q>(x[r][j][e], p, k);
+        const uint64_t b = __ballot(code[e] == kSent) & valid_lanes<W>(left, j, e);
+        cnt += (unsigned)__popcll(b);
+        flags[r] |= ((unsigned)(b >> lane) & 1u) << (W * j + e);
+      }
+      store_codes<W>(codes + (uint64_t)c * kChunk, (unsigned)(64 * W * j + W * lane), left, code);
+    }
+    if (lane == 0) s_cnt[c] = cnt;
+  }
+  __syncthreads();
+  // every wavefront scans the counts for itself
+  const unsigned cc = s_cnt[lane];
+  const unsigned incl = wave_incl_add(cc);
+  const unsigned total = lane63(incl);
+  if (wave == 0 && (unsigned)lane < nch)
+    reinterpret_cast<uint64_t *>(f.stream + chunk_table_offset(n))[lane] = incl - cc;
+  U *outl = reinterpret_cast<U *>(f.stream + outlier_offset(n));
+#pragma unroll
+  for (int r = 0; r < K; r++) {
+    const unsigned c = (unsigned)(r * kSmallWaves + wave);
+    if (!__ballot(flags[r] != 0)) continue;  // uniform; also past the end
+    unsigned at = (unsigned)__builtin_amdgcn_readlane((int)(incl - cc), (int)c);
+#pragma unroll
+    for (int j = 0; j < NSUB; j++) {
+      unsigned q = at;
+#pragma unroll
+      for (int e = 0; e < W; e++) {
+        const uint64_t b = __ballot((flags[r] >> (W * j + e)) & 1u);
+        q = lanes_below(b, q);
+        at += (unsigned)__popcll(b);
+      }
+#pragma unroll
+      for (int e = 0; e < W; e++)
+        if ((flags[r] >> (W * j + e)) & 1u) outl[q++] = to_bits(x[r][j][e]);
+    }
+  }
+  if (tid == (kSmallWaves - 1) * 64)  // (the wavefront with the fewest chunks)
+    finish_stream<T>(f.stream, f.stream_bytes, n, f.hdr, total, Q == kNOA ? &d : nullptr);
 }
 
 // ---------------------------------------------------------- dequantize ---

@@ -56,7 +56,7 @@ struct CmpArgs {
   uint64_t n;
   uint8_t *out;                // packed stream
   uint64_t *out_bytes;
-  uint32_t *counts;            // outliers per chunk
+  uint16_t *counts;            // outliers per chunk
   uint32_t *meta;              // w | mode << 8 | hb << 16 per chunk
   uint32_t *sizes;             // record bytes per chunk
   uint16_t *flags;             // per lane of a chunk with outliers: its outlier flags
@@ -164,7 +164,7 @@ __device__ __forceinline__ void stage_chunk(const CmpArgs &a, const FieldParams<
   rb = (unsigned)record_bytes(len, w, hb);
   if (hb) a.flags[c * 64 + lane] = (uint16_t)flags;
   if (lane == 0) {
-    a.counts[c] = cnt;
+    a.counts[c] = (uint16_t)cnt;
     a.meta[c] = w | (mode << 8) | (hb << 16);
     a.sizes[c] = rb;
   }
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_cmp_finish(CmpArgs a) {
   using U = typename FT<T>::U;
   __shared__ unsigned long long s_red[3][kWaves];
   __shared__ unsigned s_wt[2][kWaves];
-  __shared__ uint64_t s_P[kBlock];
+  __shared__ unsigned s_P[kBlock];
   __shared__ unsigned s_c[kBlock];
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -374,45 +374,22 @@ __global__ __launch_bounds__(kBlock) void k_cmp_finish(CmpArgs a) {
       chunk_tab[c] = run + before + (incl - cnt);
       offs[c] = rrun + sbefore + (sincl - sz);
     }
-    s_P[tid] = before + (incl - cnt);  // batch-relative first outlier of each chunk
+    s_P[tid] = (unsigned)before + (incl - cnt);  // batch-relative first outlier of each chunk
     s_c[tid] = cnt;
-    const int m = (int)min<uint64_t>((uint64_t)kBlock, c1 - cb);
     __syncthreads();  // s_P and s_c whole
-    // staged rows of chunks with at most kDirect outliers: half a wavefront
-    // per chunk, word r of a row moved by lane r of the half
-    {
-      constexpr int kHalves = kBlock / kDirect, kRound = 16;
-      static_assert(kDirect == 32, "a directly copied row is one half wavefront");
-      const int h = tid / kDirect, r = tid % kDirect;
-      for (int i0 = h; i0 < m; i0 += kHalves * kRound) {
-        U v[kRound];
-        uint64_t dst[kRound];
-        bool mv[kRound];
-#pragma unroll
-        for (int u = 0; u < kRound; u++) {
-          const int i = i0 + u * kHalves;
-          const unsigned ci = i < m ? s_c[i] : 0u;
-          mv[u] = ci <= (unsigned)kDirect && (unsigned)r < ci;
-          dst[u] = mv[u] ? run + s_P[i] + (unsigned)r : 0;
-          if (mv[u]) v[u] = f.stage[(cb + (uint64_t)i) * kCap + r];
-        }
-#pragma unroll
-        for (int u = 0; u < kRound; u++)
-          if (mv[u]) outl[dst[u]] = v[u];
-      }
-    }
+    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
     run += total;
     rrun += stotal;
     __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
   }
 
-  // chunks with more than kDirect outliers, spread over every workgroup
+  // chunks with more outliers than were staged, spread over every workgroup
   // (workgroup g takes chunks g, g + ngroups, ...): one wavefront per chunk
-  // copies its staged row or, past the stage cap, encodes the chunk again
+  // encodes it again
   for (uint64_t t0 = 0; g + t0 * a.ngroups < nch; t0 += kBlock) {
     const uint64_t c = g + (t0 + (uint64_t)tid) * a.ngroups;
     const unsigned cn = t0 == 0 ? duty0 : (c < nch ? a.counts[c] : 0u);
-    const bool ov = cn > (unsigned)kDirect;
+    const bool ov = cn > kCap;
     if (!__syncthreads_or(ov)) continue;
     const uint64_t wb = __ballot(ov);
     if (lane == 0) s_wt[0][wave] = (unsigned)__popcll(wb);
@@ -423,17 +400,13 @@ __global__ __launch_bounds__(kBlock) void k_cmp_finish(CmpArgs a) {
       if (w < wave) base += s_wt[0][w];
       nov += s_wt[0][w];
     }
-    if (ov) {
-      s_P[base + lanes_below(wb, 0u)] = c;
-      s_c[base + lanes_below(wb, 0u)] = cn;
-    }
+    if (ov) s_P[base + lanes_below(wb, 0u)] = (unsigned)c;
     __syncthreads();
     for (unsigned i = (unsigned)wave; i < nov; i += kWaves) {
       const uint64_t cv = s_P[i];
-      const unsigned cc = s_c[i];
-      const uint64_t P = chunk_first_outlier<T>(f, cv, lane);
-      if (cc <= kCap) copy_staged<T>(f, outl, cv, P, cc, lane);
-      else rescan_encode<T, Q>(a, cmp_params<T, Q>(a), outl, cv, P, lane);
+      const int ln = pin_v(lane);
+      rescan_encode<T, Q>(a, cmp_params<T, Q>(a), outl, cv,
+                          chunk_first_outlier<T>(f, cv, ln, nullptr), ln);
     }
     __syncthreads();  // s_wt, s_P and s_c are rewritten by the next batch
   }
@@ -657,14 +630,14 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   a.n = n;
   a.out = static_cast<uint8_t *>(d_out);
   a.out_bytes = d_bytes;
-  a.counts = reinterpret_cast<uint32_t *>(ws + cw_counts_off());
+  a.counts = reinterpret_cast<uint16_t *>(ws + cw_counts_off());
   a.meta = reinterpret_cast<uint32_t *>(ws + cw_meta_off(C));
   a.sizes = reinterpret_cast<uint32_t *>(ws + cw_sizes_off(C));
   a.flags = reinterpret_cast<uint16_t *>(ws + cw_flags_off(C));
   a.stage = ws + cw_stage_off(C);
   a.group = reinterpret_cast<unsigned long long *>(ws + kCwGroups);
   a.rgroup = a.group + kMaxGroups;
-  a.tiles_per_group = tiles_per_group(stiles, kWaves * kCmpCpw);
+  a.tiles_per_group = tiles_per_group(stiles, kWaves * kCmpCpw, kGroupChunksAlone);
   a.chunks_per_group = a.tiles_per_group * kWaves * kCmpCpw;
   a.ngroups = std::max<uint64_t>(1, (stiles + a.tiles_per_group - 1) / a.tiles_per_group);
   a.noa = reinterpret_cast<const DevParams *>(ws + kCwParams);

@@ -1,0 +1,64 @@
+"""Where quantize changes its route: one workgroup for small fields (the
+limits differ by dtype and quantizer), pass-1 workgroups' totals or atomic
+group sums.  Streams at and just past each limit must equal the oracle's
+byte for byte, with output and workspace full of garbage before the call,
+with outliers in smooth data, in every value, and with no finite value at
+all (NOA's empty range)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from gpu_util import announce, first_diff
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu_stream(q, x, eb):
+    import torch
+    import paper_2407_15037_amd as lcq
+    xt = torch.from_numpy(x).cuda()
+    ws = torch.full((lcq.workspace_bytes(q, xt.dtype, x.size),), 0xA5, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((lcq.max_stream_bytes(xt.dtype, x.size),), 0x5A, dtype=torch.uint8,
+                     device="cuda")
+    buf, nb = lcq.quantize(xt, q, eb, out=out, ws=ws)
+    return buf[: int(nb.item())].cpu().numpy()
+
+
+def _data(kind, dt, n, q, eb):
+    x = synth.sines_1d(n, n % 1000, dtype=dt)
+    if kind == "nan":
+        return np.full(n, np.nan, dt)
+    if kind == "bits":
+        ub = np.uint64 if dt == np.float64 else np.uint32
+        return np.random.default_rng(n).integers(0, np.iinfo(ub).max, n, dtype=ub).view(dt)
+    if q == "noa":
+        return synth.with_specials(x, "noa", max(19, n // 300), 3, eb)
+    x, _, _ = synth.inject_specials(x, max(19, n // 300), 3, eb)
+    return x
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("q", ["abs", "rel", "noa"])
+@pytest.mark.parametrize("n", [1, 3, 1024, 1025, 16 * 1024, 16 * 1024 + 1, 18 * 1024,
+                               18 * 1024 + 1, 24 * 1024 - 5, 24 * 1024 + 1, 32 * 1024,
+                               32 * 1024 + 1])
+def test_small_field_limits(dt, q, n):
+    for kind in ("smooth", "bits", "nan"):
+        x = _data(kind, dt, n, q, 1e-3)
+        announce("small field", np.dtype(dt).name, q, n, kind)
+        assert first_diff(_gpu_stream(q, x, 1e-3), O.quantize(q, x, 1e-3)) is None, kind
+
+
+# 2048 pass-1 workgroups of 8 (float32) or 4 (float64) chunks, and one more
+@pytest.mark.parametrize("dt,n", [(np.float32, 2048 * 8 * 1024), (np.float32, 2048 * 8 * 1024 + 1),
+                                  (np.float64, 2048 * 4 * 1024), (np.float64, 2048 * 4 * 1024 + 1)])
+def test_totals_limit(dt, n):
+    x = synth.sines_1d(n, 11, dtype=dt)
+    x[::977] = np.nan              # about one per chunk
+    x[n // 2: n // 2 + 40 * 1024: 9] = np.nan    # 114 per chunk
+    x[n // 4: n // 4 + 300 * 1024: 3] = np.nan   # 342 per chunk: over either stage cap
+    x[n - 700:] = np.nan
+    announce("totals limit", np.dtype(dt).name, n)
+    assert first_diff(_gpu_stream("abs", x, 1e-3), O.quantize_mt("abs", x, 1e-3)) is None
