@@ -10,23 +10,25 @@
 // is reading the input twice, once to size the records and once to write
 // them: the second pass takes the outliers from the first pass's flags and
 // recomputes only the bins, with the same operations as the encoder, so
-// both passes see the same codes.
+// both passes see the same codes.  (One pass with a decoupled look-back over
+// the record sizes measured 453 us and more against 227 on the 512^3 float32
+// field: the waiting workgroups' polls across XCDs are the cost.)
 //
 // Kernels (one wavefront per 1024-value chunk, the chunk kernels' lane
 // layout, lcq_chunk.hpp):
 //   k_cmp_stage   pass 1: classify / bin / reconstruct / verify (sections
-//                 2.2, 3.1-3.3) of each value; the chunk's outliers staged as
-//                 in the two-pass quantize; its record's width, mode and
-//                 size; per workgroup one atomic add of its outlier count and
-//                 one of its record bytes into its group's sums
-//   k_cmp_finish  pass 2, one workgroup per group: chunk table and record
-//                 offsets (two exclusive scans), outliers copied to their
-//                 place behind the payload, and (last group) header, padding
-//                 and size
+//                 2.2, 3.1-3.3) of each value; the chunk's outlier flags and
+//                 count, its record's width, mode and size; per workgroup its
+//                 totals, or (large fields) atomic adds into its group's sums
+//   k_cmp_scan    large fields only, one workgroup per group: chunk table and
+//                 record offsets (two exclusive scans), and (last group)
+//                 header, padding and size
 //   k_cmp_write   pass 3: each chunk's codes again from the input -- the
 //                 outliers as pass 1 flagged them, the other values' bins
 //                 recomputed -- and its record (header, outlier bitmap,
-//                 packed bits assembled in LDS) written at its offset
+//                 packed bits assembled in LDS) written at its offset, its
+//                 outliers from registers behind the payload; up to
+//                 kMaxCmpDirect workgroups, also the offsets themselves
 //   k_decompress  per chunk: record checks, codes from the record's bits,
 //                 then the dequantize path's decode and outlier gather
 //                 (section 3) and one store of the values
@@ -51,6 +53,13 @@ using namespace lcq;
 
 namespace {
 
+// Up to this many workgroups (of kWaves chunks) pass 3 finds its own offsets
+// from pass 1's totals, 8 KiB read from L2 by each: no clear kernel before
+// and no scan kernel between (31.2 to 24.9 us for a 5 M value float64 field).
+// Above it the scan is worth its launch (at 4096 workgroups 38.0 us with it,
+// 39.5 without).
+constexpr unsigned kMaxCmpDirect = 2048;
+
 struct CmpArgs {
   const void *in;
   uint64_t n;
@@ -60,14 +69,16 @@ struct CmpArgs {
   uint32_t *meta;              // w | mode << 8 | hb << 16 per chunk
   uint32_t *sizes;             // record bytes per chunk
   uint16_t *flags;             // per lane of a chunk with outliers: its outlier flags
-  void *stage;                 // stage_cap<T>() raw outliers per chunk
+  uint32_t *totals;            // per workgroup: record bytes / 16 << 16 | outliers, or null:
   unsigned long long *group;   // outliers per group of workgroups
   unsigned long long *rgroup;  // record bytes per group
+  uint64_t ntiles;
   uint64_t tiles_per_group, chunks_per_group, ngroups;
   const DevParams *noa;        // NOA: parameters computed on the device
   uint64_t step, inv, bound, low;  // ABS / REL parameters (raw bits)
   uint64_t hdr[8];                 // header of the packed stream
 };
+static_assert(kWaves * kChunk < 65536 && kWaves * kMaxRecord / 16 < 65536, "totals fit 16 bits each");
 
 template <typename T, int Q>
 __device__ __forceinline__ FieldParams<T> cmp_params(const CmpArgs &a) {
@@ -82,82 +93,46 @@ __device__ __forceinline__ FieldParams<T> cmp_params(const CmpArgs &a) {
   return p;
 }
 
-// Codes of chunk c (values x in the chunk lane layout) as c' values --
-// the code, or 0 for an outlier -- and the outlier flags (bit W j + e: the
-// lane's position j, e, below len).  STAGE: the first stage_cap<T>()
-// outliers also go, at their ranks, through the wavefront's LDS row srow to
-// stage_row, as encode_chunk stages them.  FULL: the chunk has 1024 values.
-// Returns the chunk's outlier count.
-template <typename T, int Q, bool STAGE, bool FULL>
+// Codes of a chunk (values x in the chunk lane layout) as c' values -- the
+// code, or 0 for an outlier -- and the outlier flags (bit W j + e: the lane's
+// position j, e, below len).  FULL: the chunk has 1024 values.  Returns the
+// chunk's outlier count.
+template <typename T, int Q, bool FULL>
 __device__ __forceinline__ unsigned encode_keep(
     const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W], const FieldParams<T> &p,
-    const EncK<T> &k, unsigned len, int lane, typename FT<T>::U *srow,
-    typename FT<T>::U *stage_row, uint32_t (&cv)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
-    unsigned &flags) {
+    const EncK<T> &k, unsigned len, int lane,
+    uint32_t (&cv)[ChunkShape<T>::NSUB][ChunkShape<T>::W], unsigned &flags) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  constexpr unsigned kCap = (unsigned)stage_cap<T>();
   unsigned cnt = 0;
   flags = 0;
 #pragma unroll
   for (int j = 0; j < NSUB; j++) {
     const unsigned pos = chunk_pos<W>(j, lane);
-    bool fs[W];
-    uint64_t b[W], any = 0;
 #pragma unroll
     for (int e = 0; e < W; e++) {
-      const int32_t code = encode<T, Q>(x[j][e], p, k);
+      // (pinned in the ragged copy: see encode_chunk_at)
+      const int32_t code = encode<T, Q>(FULL ? x[j][e] : pin_v(x[j][e]), p, k);
       const bool s = code == kSent;
-      fs[e] = FULL ? s : (s && pos + e < len);
-      b[e] = __ballot(fs[e]);
-      any |= b[e];
+      const bool fs = FULL ? s : (s && pos + e < len);
+      cnt += (unsigned)__popcll(__ballot(fs));
       cv[j][e] = s ? 0u : (uint32_t)code;
-      flags |= (fs[e] ? 1u : 0u) << (W * j + e);
+      flags |= (fs ? 1u : 0u) << (W * j + e);
     }
-    if (any) {  // uniform
-      unsigned r = cnt;
-#pragma unroll
-      for (int e = 0; e < W; e++) {
-        r = lanes_below(b[e], r);
-        cnt += (unsigned)__popcll(b[e]);
-      }
-      if constexpr (STAGE) {
-#pragma unroll
-        for (int e = 0; e < W; e++) {
-          if (fs[e]) {
-            if (r < kCap) srow[r] = to_bits(x[j][e]);
-            r++;
-          }
-        }
-      }
-    }
-  }
-  if constexpr (STAGE) {
-    // other lanes' LDS writes, then this lane's reads: LDS accesses of one
-    // wavefront complete in issue order, so a wavefront-scope fence orders
-    // them
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    const unsigned staged = min(cnt, kCap);  // uniform
-    for (unsigned b0 = 0; b0 < staged; b0 += 64)
-      if (b0 + (unsigned)lane < staged) stage_row[b0 + lane] = srow[b0 + lane];
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
   return cnt;
 }
 
-// Pass 1 for one chunk: its outliers staged, its count, width, mode and
-// record size (all lanes get the count and the record size).
+// Pass 1 for one chunk: its outlier flags and count, width, mode and record
+// size (all lanes get the count and the record size).
 template <typename T, int Q, bool FULL>
 __device__ __forceinline__ void stage_chunk(const CmpArgs &a, const FieldParams<T> &p,
                                             const EncK<T> &k, uint64_t c, unsigned len, int lane,
                                             const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
-                                            typename FT<T>::U *srow, unsigned &cnt, unsigned &rb) {
-  using U = typename FT<T>::U;
+                                            unsigned &cnt, unsigned &rb) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  constexpr unsigned kCap = (unsigned)stage_cap<T>();
   uint32_t cv[NSUB][W];
   unsigned flags;
-  cnt = encode_keep<T, Q, true, FULL>(x, p, k, len, lane, srow,
-                                      static_cast<U *>(a.stage) + c * kCap, cv, flags);
+  cnt = encode_keep<T, Q, FULL>(x, p, k, len, lane, cv, flags);
   unsigned w, mode;
   chunk_width<FULL, W, NSUB>(cv, len, lane, w, mode);
   const unsigned hb = cnt ? 1u : 0u;
@@ -195,44 +170,28 @@ __device__ __forceinline__ void load_chunk_cached(const T *in, uint64_t n, uint6
   }
 }
 
-// Pass 1 for the kCmpCpw * kWaves chunks of workgroup blockIdx.x: chunk
-// (tile kCmpCpw + r) kWaves + wave in round r, every round's input loaded
-// before the first is encoded.  (2 and 4 chunks per wavefront measured
-// slower than 1 on the 512^3 float32 field: compress 263-272 us against
-// 253 us for ABS; their registers cost more occupancy than the extra loads
-// in flight gain.)
-constexpr int kCmpCpw = 1;
-
+// Pass 1, one chunk per wavefront.  (2 and 4 measured slower on the 512^3
+// float32 field: compress 263-272 us against 253 us for ABS; their registers
+// cost more occupancy than the extra loads in flight gain.  float32 is held to
+// 64 registers, 8 wavefronts per SIMD: 227 to 221 us; float64 at 7 or 8 per
+// SIMD spills, 196 to 216 us REL, and is left to the compiler.)
 template <typename T, int Q>
-__global__ __launch_bounds__(kBlock) void k_cmp_stage(CmpArgs a) {
-  using U = typename FT<T>::U;
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 8 : 1) void k_cmp_stage(CmpArgs a) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  constexpr unsigned kCap = (unsigned)stage_cap<T>();
   __shared__ unsigned s_cnt[kWaves], s_rb[kWaves];
-  __shared__ U s_stage[kWaves][kCap];  // one row per wavefront
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk logic is scalar
   const uint64_t n = a.n, nch = n_chunks(n);
   const FieldParams<T> p = cmp_params<T, Q>(a);
   const EncK<T> k = enc_consts_pinned<T, Q>(p);
   unsigned cnt = 0, rb = 0;
-  T x[kCmpCpw][NSUB][W];
-#pragma unroll
-  for (int r = 0; r < kCmpCpw; r++) {
-    const uint64_t c = ((uint64_t)blockIdx.x * kCmpCpw + r) * kWaves + wave;
-    if (c < nch) load_chunk_cached<T>(static_cast<const T *>(a.in), n, c, lane, x[r]);
-  }
-#pragma unroll
-  for (int r = 0; r < kCmpCpw; r++) {
-    const uint64_t c = ((uint64_t)blockIdx.x * kCmpCpw + r) * kWaves + wave;
-    if (c < nch) {  // uniform over the wavefront
-      const unsigned len = chunk_len(n, c);
-      unsigned cc, rr;
-      if (len == kChunk) stage_chunk<T, Q, true>(a, p, k, c, len, lane, x[r], s_stage[wave], cc, rr);
-      else stage_chunk<T, Q, false>(a, p, k, c, len, lane, x[r], s_stage[wave], cc, rr);
-      cnt += cc;
-      rb += rr;
-    }
+  const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+  if (c < nch) {  // uniform over the wavefront
+    T x[NSUB][W];
+    load_chunk_cached<T>(static_cast<const T *>(a.in), n, c, lane, x);
+    const unsigned len = chunk_len(n, c);
+    if (len == kChunk) stage_chunk<T, Q, true>(a, p, k, c, len, lane, x, cnt, rb);
+    else stage_chunk<T, Q, false>(a, p, k, c, len, lane, x, cnt, rb);
   }
   if (lane == 0) {
     s_cnt[wave] = cnt;
@@ -240,114 +199,89 @@ __global__ __launch_bounds__(kBlock) void k_cmp_stage(CmpArgs a) {
   }
   __syncthreads();
   if (tid == 0) {
-    unsigned long long t = 0, r = 0;
+    unsigned t = 0, r = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; w++) {
       t += s_cnt[w];
       r += s_rb[w];
     }
-    const uint64_t g = blockIdx.x / a.tiles_per_group;
-    if (t) atomicAdd(a.group + g, t);
-    if (r) atomicAdd(a.rgroup + g, r);
-  }
-}
-
-// Outliers of chunk c found by encoding it again (a chunk with more
-// outliers than were staged), written to outl from index P on.  One
-// wavefront.
-template <typename T, int Q>
-__device__ void rescan_encode(const CmpArgs &a, const FieldParams<T> &p,
-                              typename FT<T>::U *outl, uint64_t c, uint64_t P, int lane) {
-  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  const EncK<T> k = enc_consts<T, Q>(p);
-  const uint64_t n = a.n;
-  T x[NSUB][W];
-  load_chunk<T>(static_cast<const T *>(a.in), n, c, lane, x);
-  const uint64_t left = n - c * kChunk;
-  uint64_t run = P;
-#pragma unroll
-  for (int j = 0; j < NSUB; j++) {
-    uint64_t b[W];
-    uint64_t r = run;
-#pragma unroll
-    for (int e = 0; e < W; e++) {
-      b[e] = __ballot(encode<T, Q>(x[j][e], p, k) == kSent) & valid_lanes<W>(left, j, e);
-      r = lanes_below(b[e], (unsigned)0) + r;
-      run += (uint64_t)__popcll(b[e]);
+    if (a.totals) {
+      a.totals[blockIdx.x] = (r / 16) << 16 | t;
+    } else {
+      const uint64_t g = blockIdx.x / a.tiles_per_group;
+      if (t) atomicAdd(a.group + g, (unsigned long long)t);
+      if (r) atomicAdd(a.rgroup + g, (unsigned long long)r);
     }
-#pragma unroll
-    for (int e = 0; e < W; e++)
-      if ((b[e] >> lane) & 1u) outl[r++] = to_bits(x[j][e]);
   }
 }
 
-// Pass 2 for group g.  The outliers' place follows the payload, whose size
-// (all groups' record bytes) every workgroup sums for itself.
+// Header (k outliers), padding and size of the packed stream, by one thread.
 template <typename T, int Q>
-__global__ __launch_bounds__(kBlock) void k_cmp_finish(CmpArgs a) {
-  using U = typename FT<T>::U;
-  __shared__ unsigned long long s_red[3][kWaves];
+__device__ __forceinline__ void finish_packed(const CmpArgs &a, uint64_t payload, uint64_t k) {
+  const uint64_t nch = n_chunks(a.n);
+  const uint64_t ot = packed_table_offset(nch), pl = packed_payload_offset(nch);
+  const uint64_t oo = align16(pl + payload);
+  uint64_t h[8];
+#pragma unroll
+  for (int i = 0; i < 8; i++) h[i] = a.hdr[i];
+  h[2] = k;
+  if constexpr (Q == kNOA) {
+    h[4] = a.noa->step;
+    h[5] = a.noa->bound;
+    h[6] = a.noa->lo;
+    h[7] = a.noa->hi;
+  }
+  uint64_t *hd = reinterpret_cast<uint64_t *>(a.out);
+#pragma unroll
+  for (int i = 0; i < 8; i++) hd[i] = h[i];
+  reinterpret_cast<uint64_t *>(a.out + ot)[nch] = payload;
+  for (uint64_t x = 64 + 8 * nch; x < ot; x++) a.out[x] = 0;
+  for (uint64_t x = ot + 8 * (nch + 1); x < pl; x++) a.out[x] = 0;
+  for (uint64_t x = pl + payload; x < oo; x++) a.out[x] = 0;
+  *a.out_bytes = oo + k * sizeof(T);
+}
+
+// Pass 2 for group g: chunk table and record offsets.
+template <typename T, int Q>
+__global__ __launch_bounds__(kBlock) void k_cmp_scan(CmpArgs a) {
+  __shared__ unsigned long long s_red[2][kWaves];
   __shared__ unsigned s_wt[2][kWaves];
-  __shared__ unsigned s_P[kBlock];
-  __shared__ unsigned s_c[kBlock];
-  constexpr unsigned kCap = (unsigned)stage_cap<T>();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t g = blockIdx.x;
-  const uint64_t n = a.n, nch = n_chunks(n);
-  const uint64_t ot = packed_table_offset(nch), pl = packed_payload_offset(nch);
-  FinishField<T> f{};
-  f.in = static_cast<const T *>(a.in);
-  f.n = n;
-  f.stream = a.out;
-  f.counts = a.counts;
-  f.stage = static_cast<const U *>(a.stage);
-  f.group = a.group;
-  f.chunks_per_group = a.chunks_per_group;
-  f.ngroups = a.ngroups;
-
+  const uint64_t nch = n_chunks(a.n);
   const uint64_t c0 = g * a.chunks_per_group;
   const uint64_t c1 = min(c0 + a.chunks_per_group, nch);
-  // the first batch's counts and sizes, and the first heavy-chunk duty
-  // count, are loaded before the group sums are reduced
+  // the first batch's counts and sizes are loaded before the group sums are
+  // reduced
   unsigned cnt_next = c0 + tid < c1 ? a.counts[c0 + tid] : 0u;
   unsigned sz_next = c0 + tid < c1 ? a.sizes[c0 + tid] : 0u;
-  const uint64_t cd0 = g + (uint64_t)tid * a.ngroups;
-  const unsigned duty0 = cd0 < nch ? a.counts[cd0] : 0u;
-
-  // outliers and record bytes of the earlier groups, and the record bytes
-  // of all groups (unconditional loads at a clamped index, masked after)
+  // outliers and record bytes of the earlier groups (unconditional loads at
+  // a clamped index, masked after)
   static_assert(kMaxGroups % kBlock == 0, "whole rounds of group sums");
-  unsigned long long bo = 0, br = 0, bt = 0;
+  unsigned long long bo = 0, br = 0;
 #pragma unroll
   for (int r = 0; r < (int)(kMaxGroups / kBlock); r++) {
     const uint64_t i = (uint64_t)tid + (uint64_t)r * kBlock;
     const unsigned long long vo = a.group[i < g ? i : 0];
-    const unsigned long long vr = a.rgroup[i < a.ngroups ? i : 0];
+    const unsigned long long vr = a.rgroup[i < g ? i : 0];
     bo += i < g ? vo : 0ull;
     br += i < g ? vr : 0ull;
-    bt += i < a.ngroups ? vr : 0ull;
   }
   bo = wave_sum(bo);
   br = wave_sum(br);
-  bt = wave_sum(bt);
   if (lane == 0) {
     s_red[0][wave] = bo;
     s_red[1][wave] = br;
-    s_red[2][wave] = bt;
   }
   __syncthreads();
-  uint64_t run = 0, rrun = 0, payload = 0;
+  uint64_t run = 0, rrun = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; w++) {
     run += s_red[0][w];
     rrun += s_red[1][w];
-    payload += s_red[2][w];
   }
-  const uint64_t oo = align16(pl + payload);
-  U *outl = reinterpret_cast<U *>(a.out + oo);
   uint64_t *chunk_tab = reinterpret_cast<uint64_t *>(a.out + 64);
-  uint64_t *offs = reinterpret_cast<uint64_t *>(a.out + ot);
-
+  uint64_t *offs = reinterpret_cast<uint64_t *>(a.out + packed_table_offset(nch));
   for (uint64_t cb = c0; cb < c1; cb += kBlock) {
     const uint64_t c = cb + tid;
     const unsigned cnt = cnt_next, sz = sz_next;
@@ -374,64 +308,11 @@ __global__ __launch_bounds__(kBlock) void k_cmp_finish(CmpArgs a) {
       chunk_tab[c] = run + before + (incl - cnt);
       offs[c] = rrun + sbefore + (sincl - sz);
     }
-    s_P[tid] = (unsigned)before + (incl - cnt);  // batch-relative first outlier of each chunk
-    s_c[tid] = cnt;
-    __syncthreads();  // s_P and s_c whole
-    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
     run += total;
     rrun += stotal;
-    __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
+    __syncthreads();  // s_wt is rewritten by the next batch
   }
-
-  // chunks with more outliers than were staged, spread over every workgroup
-  // (workgroup g takes chunks g, g + ngroups, ...): one wavefront per chunk
-  // encodes it again
-  for (uint64_t t0 = 0; g + t0 * a.ngroups < nch; t0 += kBlock) {
-    const uint64_t c = g + (t0 + (uint64_t)tid) * a.ngroups;
-    const unsigned cn = t0 == 0 ? duty0 : (c < nch ? a.counts[c] : 0u);
-    const bool ov = cn > kCap;
-    if (!__syncthreads_or(ov)) continue;
-    const uint64_t wb = __ballot(ov);
-    if (lane == 0) s_wt[0][wave] = (unsigned)__popcll(wb);
-    __syncthreads();
-    unsigned base = 0, nov = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; w++) {
-      if (w < wave) base += s_wt[0][w];
-      nov += s_wt[0][w];
-    }
-    if (ov) s_P[base + lanes_below(wb, 0u)] = (unsigned)c;
-    __syncthreads();
-    for (unsigned i = (unsigned)wave; i < nov; i += kWaves) {
-      const uint64_t cv = s_P[i];
-      const int ln = pin_v(lane);
-      rescan_encode<T, Q>(a, cmp_params<T, Q>(a), outl, cv,
-                          chunk_first_outlier<T>(f, cv, ln, nullptr), ln);
-    }
-    __syncthreads();  // s_wt, s_P and s_c are rewritten by the next batch
-  }
-
-  if (g == a.ngroups - 1 && tid == 0) {
-    const uint64_t k = run;
-    uint64_t h[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) h[i] = a.hdr[i];
-    h[2] = k;
-    if constexpr (Q == kNOA) {
-      h[4] = a.noa->step;
-      h[5] = a.noa->bound;
-      h[6] = a.noa->lo;
-      h[7] = a.noa->hi;
-    }
-    uint64_t *hd = reinterpret_cast<uint64_t *>(a.out);
-#pragma unroll
-    for (int i = 0; i < 8; i++) hd[i] = h[i];
-    offs[nch] = payload;
-    for (uint64_t x = 64 + 8 * nch; x < ot; x++) a.out[x] = 0;
-    for (uint64_t x = ot + 8 * (nch + 1); x < pl; x++) a.out[x] = 0;
-    for (uint64_t x = pl + payload; x < oo; x++) a.out[x] = 0;
-    *a.out_bytes = oo + k * sizeof(T);
-  }
+  if (g == a.ngroups - 1 && tid == 0) finish_packed<T, Q>(a, rrun, run);
 }
 
 // c' of x: 0 for an outlier, else x's code -- its bin computed by the
@@ -452,16 +333,62 @@ __device__ __forceinline__ uint32_t bin_code(T x, const FieldParams<T> &p, bool 
   }
 }
 
+// The chunk's outliers (flags: bit W j + e of each lane) to outl, in input
+// order, from the registers that hold its values: gathered in the
+// wavefront's LDS row (before its bits are packed there) and stored in
+// contiguous runs; what does not fit the row (float64, more than 512) goes
+// directly.
+template <typename T>
+__device__ __forceinline__ void put_outliers(const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
+                                             unsigned flags, int lane, uint32_t *row,
+                                             typename FT<T>::U *outl) {
+  using U = typename FT<T>::U;
+  constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
+  constexpr unsigned kFit = 4 * kChunk / sizeof(U);
+  U *srow = reinterpret_cast<U *>(row);
+  unsigned at = 0;
+#pragma unroll
+  for (int j = 0; j < NSUB; j++) {
+    uint64_t b[W], any = 0;
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      b[e] = __ballot((flags >> (W * j + e)) & 1u);
+      any |= b[e];
+    }
+    if (!any) continue;  // uniform
+    unsigned r = at;
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      r = lanes_below(b[e], r);
+      at += (unsigned)__popcll(b[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < W; e++)
+      if ((flags >> (W * j + e)) & 1u) {
+        if (kFit >= kChunk || r < kFit) srow[r] = to_bits(x[j][e]);
+        else outl[r] = to_bits(x[j][e]);
+        r++;
+      }
+  }
+  // (LDS accesses of one wavefront complete in issue order)
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const unsigned fit = min(at, kFit);  // uniform
+  for (unsigned i = (unsigned)lane; i < fit; i += 64) outl[i] = srow[i];
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
 // Pass 3 for one chunk: its c' values again (the first pass's outlier
-// flags, the bins recomputed), its record written at rec.
+// flags, the bins recomputed), its record written at rec, its outliers (by
+// rank) at outl.
 template <typename T, int Q, bool FULL>
 __device__ __forceinline__ void write_chunk(const CmpArgs &a, const FieldParams<T> &p, uint64_t c,
                                             uint32_t m, unsigned len, int lane,
                                             const T (&x)[ChunkShape<T>::NSUB][ChunkShape<T>::W],
-                                            uint32_t *row, uint8_t *rec) {
+                                            uint32_t *row, uint8_t *rec, typename FT<T>::U *outl) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
   const unsigned w = m & 0xFF, mode = (m >> 8) & 1, hb = (m >> 16) & 1;
   const unsigned flags = hb ? (unsigned)a.flags[c * 64 + lane] : 0u;
+  if (hb) put_outliers<T>(x, flags, lane, row, outl);
   uint32_t cv[NSUB][W];
 #pragma unroll
   for (int j = 0; j < NSUB; j++) {
@@ -470,7 +397,7 @@ __device__ __forceinline__ void write_chunk(const CmpArgs &a, const FieldParams<
     for (int e = 0; e < W; e++) {
       // positions past the end count as outliers: c' 0, no bin computed
       const bool out = ((flags >> (W * j + e)) & 1u) != 0 || (!FULL && pos + e >= len);
-      cv[j][e] = bin_code<T, Q>(x[j][e], p, out);
+      cv[j][e] = bin_code<T, Q>(FULL ? x[j][e] : pin_v(x[j][e]), p, out);
     }
   }
   uint32_t z[NSUB][W];
@@ -482,24 +409,96 @@ __device__ __forceinline__ void write_chunk(const CmpArgs &a, const FieldParams<
              lane);
 }
 
-template <typename T, int Q>
-__global__ __launch_bounds__(kBlock) void k_cmp_write(CmpArgs a) {
+// Record bytes / 16 and outliers of the workgroups before `tile`, and of all
+// (a.totals), to every thread of the workgroup.
+struct CmpSums {
+  uint32_t bytes16, outliers, all_bytes16, all_outliers;
+};
+__device__ __forceinline__ CmpSums sum_totals(const CmpArgs &a, unsigned tile) {
+  __shared__ uint32_t s_sum[4][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(kMaxCmpDirect == 8 * kBlock, "two loads of four per thread");
+  const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(a.totals);
+  const unsigned nt = (unsigned)a.ntiles;
+  uint32_t v[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    const unsigned i = (unsigned)(tid + k * kBlock);
+    if (4u * (unsigned)(k * kBlock) < nt) {  // uniform
+      const nt_i4 q = tot[4 * i < nt ? i : 0];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const unsigned t = 4 * i + u;
+        const uint32_t w = t < nt ? (uint32_t)q[u] : 0u;  // (words past the last are garbage)
+        v[0] += t < tile ? w >> 16 : 0u;
+        v[1] += t < tile ? w & 0xFFFFu : 0u;
+        v[2] += w >> 16;
+        v[3] += w & 0xFFFFu;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const uint32_t t = lane63(wave_incl_add(v[q]));
+    if (lane == 0) s_sum[q][wave] = t;
+  }
+  __syncthreads();
+  uint32_t r[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 4; q++)
+#pragma unroll
+    for (int w = 0; w < kWaves; w++) r[q] += s_sum[q][w];
+  return CmpSums{r[0], r[1], r[2], r[3]};
+}
+
+// DIRECT: offsets from the totals (no scan kernel ran).  (float32 spills at 8
+// wavefronts per SIMD: 512^3 ABS compress 217.4 us, REL 270; with 7, 215.9
+// and 269.)
+template <typename T, int Q, bool DIRECT>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? 1 : 7) void k_cmp_write(CmpArgs a) {
+  using U = typename FT<T>::U;
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
-  __shared__ uint32_t s_w[kWaves][kChunk];  // each wavefront's packed words
+  __shared__ __align__(16) uint32_t s_w[kWaves][kChunk];  // each wavefront's packed words
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t n = a.n, nch = n_chunks(n);
   const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
-  if (c >= nch) return;  // uniform over the wavefront; no barrier follows
+  const bool act = c < nch;  // uniform over the wavefront
   const uint64_t ot = packed_table_offset(nch), pl = packed_payload_offset(nch);
+  uint64_t *chunk_tab = reinterpret_cast<uint64_t *>(a.out + 64);
+  uint64_t *offs = reinterpret_cast<uint64_t *>(a.out + ot);
+  T x[NSUB][W];
+  if (act) load_chunk<T>(static_cast<const T *>(a.in), n, c, lane, x);
+  uint64_t off, first, payload;
+  if constexpr (DIRECT) {
+    const CmpSums s = sum_totals(a, blockIdx.x);
+    off = 16ull * s.bytes16;
+    first = s.outliers;
+    payload = 16ull * s.all_bytes16;
+    for (int i = 0; i < wave; i++) {  // this workgroup's earlier chunks
+      off += a.sizes[(uint64_t)blockIdx.x * kWaves + i];
+      first += a.counts[(uint64_t)blockIdx.x * kWaves + i];
+    }
+    if (act && lane == 0) {
+      offs[c] = off;
+      chunk_tab[c] = first;
+    }
+    if (blockIdx.x == a.ntiles - 1 && threadIdx.x == kBlock - 1)
+      finish_packed<T, Q>(a, payload, s.all_outliers);
+    if (!act) return;  // no barrier follows
+  } else {
+    if (!act) return;  // no barrier at all
+    off = offs[c];
+    first = chunk_tab[c];
+    payload = offs[nch];
+  }
   const FieldParams<T> p = cmp_params<T, Q>(a);
   const uint32_t m = a.meta[c];
   const unsigned len = chunk_len(n, c);
-  uint8_t *rec = a.out + pl + reinterpret_cast<const uint64_t *>(a.out + ot)[c];
-  T x[NSUB][W];
-  load_chunk<T>(static_cast<const T *>(a.in), n, c, lane, x);
-  if (len == kChunk) write_chunk<T, Q, true>(a, p, c, m, len, lane, x, s_w[wave], rec);
-  else write_chunk<T, Q, false>(a, p, c, m, len, lane, x, s_w[wave], rec);
+  uint8_t *rec = a.out + pl + off;
+  U *outl = reinterpret_cast<U *>(a.out + align16(pl + payload)) + first;
+  if (len == kChunk) write_chunk<T, Q, true>(a, p, c, m, len, lane, x, s_w[wave], rec, outl);
+  else write_chunk<T, Q, false>(a, p, c, m, len, lane, x, s_w[wave], rec, outl);
 }
 
 struct DcmpArgs {
@@ -590,8 +589,10 @@ __global__ void k_clear_cmp(uint64_t *p, uint64_t count) {
 // [256, ...)  outliers per group, then record bytes per group (kMaxGroups
 //             each), cleared by every compress
 // then        counts, meta and record sizes (4 bytes per chunk each), the
-//             outlier flags (2 bytes per lane of a chunk), the staged
-//             outliers (stage_cap<T>() per chunk), NOA's range pairs
+//             outlier flags (2 bytes per lane of a chunk), NOA's range pairs
+//             (behind room for stage_cap<T>() values per chunk that earlier
+//             layouts kept: the size callers were told stays).  Counts take
+//             2 of their 4 bytes per chunk; the totals follow them there.
 constexpr uint64_t kCwParams = 64, kCwGroups = 256;
 uint64_t al256(uint64_t v) { return (v + 255) & ~255ull; }
 uint64_t cw_counts_off() { return al256(kCwGroups + 16 * kMaxGroups); }
@@ -623,8 +624,7 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   const HostParams hp = host_params<T>(Q, eb);
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
   const uint64_t C = n_chunks(n);
-  const uint64_t ntiles = (C + kWaves - 1) / kWaves;  // pass 3: one chunk per wavefront
-  const uint64_t stiles = (C + kWaves * kCmpCpw - 1) / (kWaves * kCmpCpw);  // pass 1
+  const uint64_t ntiles = (C + kWaves - 1) / kWaves;
   CmpArgs a{};
   a.in = d_in;
   a.n = n;
@@ -634,12 +634,14 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   a.meta = reinterpret_cast<uint32_t *>(ws + cw_meta_off(C));
   a.sizes = reinterpret_cast<uint32_t *>(ws + cw_sizes_off(C));
   a.flags = reinterpret_cast<uint16_t *>(ws + cw_flags_off(C));
-  a.stage = ws + cw_stage_off(C);
   a.group = reinterpret_cast<unsigned long long *>(ws + kCwGroups);
   a.rgroup = a.group + kMaxGroups;
-  a.tiles_per_group = tiles_per_group(stiles, kWaves * kCmpCpw, kGroupChunksAlone);
-  a.chunks_per_group = a.tiles_per_group * kWaves * kCmpCpw;
-  a.ngroups = std::max<uint64_t>(1, (stiles + a.tiles_per_group - 1) / a.tiles_per_group);
+  a.ntiles = ntiles;
+  if (ntiles && ntiles <= kMaxCmpDirect)
+    a.totals = reinterpret_cast<uint32_t *>(ws + align16(cw_counts_off() + 2 * C));
+  a.tiles_per_group = tiles_per_group(ntiles, kWaves);
+  a.chunks_per_group = a.tiles_per_group * kWaves;
+  a.ngroups = std::max<uint64_t>(1, (ntiles + a.tiles_per_group - 1) / a.tiles_per_group);
   a.noa = reinterpret_cast<const DevParams *>(ws + kCwParams);
   a.step = hp.step;
   a.inv = hp.inv;
@@ -654,21 +656,25 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   a.hdr[6] = hp.aux0;
   a.hdr[7] = hp.aux1;
   uint64_t *clear_ptr = reinterpret_cast<uint64_t *>(a.group);
-  const uint64_t clear_count = 2 * kMaxGroups;
+  const uint64_t clear_count = a.totals ? 0 : 2 * kMaxGroups;
   if (Q == kNOA) {
     T *partials = reinterpret_cast<T *>(ws + cw_partials_off((lcq_dtype)dt, C));
     launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr, clear_count,
                         from_bits((typename FT<T>::U)hp.eb_down),
                         reinterpret_cast<DevParams *>(ws + kCwParams), s);
-  } else {
+  } else if (clear_count) {
     hipLaunchKernelGGL(k_clear_cmp, dim3((unsigned)(clear_count / kBlock)), dim3(kBlock), 0, s,
                        clear_ptr, clear_count);
   }
   if (ntiles)
-    hipLaunchKernelGGL((k_cmp_stage<T, Q>), dim3((unsigned)stiles), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL((k_cmp_finish<T, Q>), dim3((unsigned)a.ngroups), dim3(kBlock), 0, s, a);
-  if (ntiles)
-    hipLaunchKernelGGL((k_cmp_write<T, Q>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((k_cmp_stage<T, Q>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  if (a.totals) {
+    hipLaunchKernelGGL((k_cmp_write<T, Q, true>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((k_cmp_scan<T, Q>), dim3((unsigned)a.ngroups), dim3(kBlock), 0, s, a);
+    if (ntiles)
+      hipLaunchKernelGGL((k_cmp_write<T, Q, false>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  }
   return check_launch_cmp();
 }
 

@@ -209,7 +209,7 @@ __device__ __forceinline__ int32_t encode(T x, const FieldParams<T> &p, const En
   using U = typename F::U;
   const U u = to_bits(x);
   bool ok = class_test(x, k.cls);
-  if (Q == kNOA) ok = ok && !p.lossless_all;
+  if (Q == kNOA) ok = ok & (p.lossless_all == 0);
 
   if constexpr (is_rel_q<Q>()) {
     // |x| (an absolute-value source modifier where it is used, not an
@@ -218,7 +218,7 @@ __device__ __forceinline__ int32_t encode(T x, const FieldParams<T> &p, const En
     // (the approximate log2 reads only the exponent and fraction fields)
     const T q = Q == kREL_LIBM ? rint_t(lib_log2(a) * p.inv) : rel_bin(x, p.inv, k.lgoff);
     // section 3.3: both range tests, on the float, before any conversion
-    ok = ok && (q > (T)-kMaxBin) && (q < (T)kMaxBin);
+    ok = ok & (q > (T)-kMaxBin) & (q < (T)kMaxBin);
     // qb is integral and inside (-2^30, 2^30), so (T)(int)qb == qb exactly
     const T qb = ok ? q : (T)0;
     const int32_t b = (int32_t)qb;
@@ -236,12 +236,14 @@ __device__ __forceinline__ int32_t encode(T x, const FieldParams<T> &p, const En
     const uint32_t code = __builtin_amdgcn_alignbit((uint32_t)b, hi, 31);
     return ok ? (int32_t)code : k.sent;
   } else {
+    // (bitwise: with && each value's tests became two branches on the
+    // execution mask, and the masks of a chunk spilled to vector lanes)
     const T q = rint_t(x * p.inv);
-    ok = ok && (q > (T)-kMaxBin) && (q < (T)kMaxBin);
+    ok = ok & (q > (T)-kMaxBin) & (q < (T)kMaxBin);
     const T qb = ok ? q : (T)0;  // integral, in range: (T)(int)qb == qb
     const int32_t b = (int32_t)qb;
     const T rec = qb * p.step;
-    if constexpr (Q != kABS_UNCHECKED) ok = ok && (abs_t(x - rec) <= p.bound);
+    if constexpr (Q != kABS_UNCHECKED) ok = ok & (abs_t(x - rec) <= p.bound);
     return ok ? b : k.sent;
   }
 }

@@ -1,6 +1,6 @@
-"""Where quantize changes its route: one workgroup for small fields (the
-limits differ by dtype and quantizer), pass-1 workgroups' totals or atomic
-group sums.  Streams at and just past each limit must equal the oracle's
+"""Where quantize and compress change their route: one workgroup for small
+fields (the limits differ by dtype and quantizer), pass-1 workgroups' totals
+or atomic group sums.  Streams at and just past each limit must equal the oracle's
 byte for byte, with output and workspace full of garbage before the call,
 with outliers in smooth data, in every value, and with no finite value at
 all (NOA's empty range)."""
@@ -62,3 +62,24 @@ def test_totals_limit(dt, n):
     x[n - 700:] = np.nan
     announce("totals limit", np.dtype(dt).name, n)
     assert first_diff(_gpu_stream("abs", x, 1e-3), O.quantize_mt("abs", x, 1e-3)) is None
+
+
+# compress: 2048 workgroups of 4 chunks, and one more
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [2048 * 4 * 1024, 2048 * 4 * 1024 + 1])
+def test_compress_totals_limit(dt, n):
+    import torch
+    import paper_2407_15037_amd as lcq
+    x = synth.sines_1d(n, 12, dtype=dt)
+    x[::977] = np.nan
+    x[n // 4: n // 4 + 300 * 1024: 3] = np.nan
+    x[n // 2: n // 2 + 5 * 1024] = np.nan   # whole chunks
+    x[n - 700:] = np.nan
+    announce("compress totals limit", np.dtype(dt).name, n)
+    xt = torch.from_numpy(x).cuda()
+    ws = torch.full((lcq.compress_workspace_bytes("abs", xt.dtype, n),), 0xA5, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((lcq.pack_max_bytes(xt.dtype, n),), 0x5A, dtype=torch.uint8, device="cuda")
+    pk, nb = lcq.compress(xt, "abs", 1e-3, out=out, ws=ws)
+    want = O.pack(O.quantize_mt("abs", x, 1e-3), dt, n)
+    assert first_diff(pk[: int(nb.item())].cpu().numpy(), want) is None
