@@ -109,20 +109,42 @@ def _q(q):
     return _QNAMES[q] if isinstance(q, str) else int(q)
 
 
-def _dtype_code(dtype):
+# torch, its dtypes' codes and its raw-stream query, looked up at the first
+# call (importing this package does not import torch).  A call's host time is
+# what a small field costs, so each wrapper does one dictionary look-up per
+# dtype, asks the library for sizes only where it allocates, and hands
+# pointers over as plain integers.
+_torch = None
+_codes = {}
+_raw_stream = None
+
+
+def _load_torch():
+    global _torch, _raw_stream
     import torch
-    if dtype == torch.float32:
-        return F32
-    if dtype == torch.float64:
-        return F64
-    raise TypeError(f"unsupported dtype {dtype}")
+    _codes.update({torch.float32: F32, torch.float64: F64})
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
+def _dtype_code(dtype):
+    if _torch is None:
+        _load_torch()
+    try:
+        return _codes[dtype]
+    except (KeyError, TypeError):
+        raise TypeError(f"unsupported dtype {dtype}") from None
 
 
 def _stream_handle(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """The HIP stream (an integer) of a torch stream, or of the current one."""
+    torch = _torch or _load_torch()
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _empty(numel, dtype, device, stream, zero=False):
@@ -130,7 +152,7 @@ def _empty(numel, dtype, device, stream, zero=False):
     torch's caching allocator cannot hand its memory to work on another
     stream while the call's kernels may still run (a temporary dropped when
     the wrapper returns is only reused by later work on the same stream)."""
-    import torch
+    torch = _torch or _load_torch()
     make = torch.zeros if zero else torch.empty
     if stream is None:
         return make(numel, dtype=dtype, device=device)
@@ -147,7 +169,7 @@ def workspace_bytes(q, dtype, n):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else 0
 
 
 def quantize(x, q, eb, *, out=None, nbytes=None, ws=None, stream=None):
@@ -156,19 +178,18 @@ def quantize(x, q, eb, *, out=None, nbytes=None, ws=None, stream=None):
     Returns (stream, nbytes): `stream` is a uint8 device tensor of capacity
     max_stream_bytes, `nbytes` a one-element int64 device tensor receiving the
     stream's size.  Buffers may be passed in to avoid allocation."""
-    import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA tensor")
     dt = _dtype_code(x.dtype)
+    qc = _q(q)
     n = x.numel()
-    cap = int(_lib.lcq_max_stream_bytes(dt, n))
     if out is None:
-        out = _empty(cap, torch.uint8, x.device, stream)
+        out = _empty(int(_lib.lcq_max_stream_bytes(dt, n)), _torch.uint8, x.device, stream)
     if nbytes is None:
-        nbytes = _empty(1, torch.int64, x.device, stream)
+        nbytes = _empty(1, _torch.int64, x.device, stream)
     if ws is None:
-        ws = _empty(int(_lib.lcq_workspace_bytes(_q(q), dt, n)), torch.uint8, x.device, stream)
-    st = _lib.lcq_quantize(_q(q), dt, float(eb), _ptr(x) if n else None, n, _ptr(out),
+        ws = _empty(int(_lib.lcq_workspace_bytes(qc, dt, n)), _torch.uint8, x.device, stream)
+    st = _lib.lcq_quantize(qc, dt, float(eb), _ptr(x) if n else None, n, _ptr(out),
                            out.numel(), _ptr(nbytes), _ptr(ws), ws.numel(),
                            _stream_handle(stream))
     _check(st, "lcq_quantize")
@@ -193,12 +214,11 @@ def quantize_noalloc(x, q, eb, *, out, nbytes, stream=None):
 def dequantize(stream_buf, dtype, n, *, stream_bytes=None, out=None, ws=None, stream=None):
     """Decode a stream (uint8 CUDA tensor) into a new (or given) tensor of n
     values.  stream_bytes defaults to the tensor's size."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
         out = _empty(n, dtype, stream_buf.device, stream)
     if ws is None:
-        ws = _empty(64, torch.uint8, stream_buf.device, stream)
+        ws = _empty(64, _torch.uint8, stream_buf.device, stream)
     sb = stream_buf.numel() if stream_bytes is None else int(stream_bytes)
     st = _lib.lcq_dequantize(dt, _ptr(stream_buf), sb, _ptr(out) if n else None, n, _ptr(ws),
                              ws.numel(), _stream_handle(stream))
@@ -213,19 +233,18 @@ def _abl(kind):
 def quantize_ablation(x, kind, eb, *, out=None, nbytes=None, ws=None, stream=None):
     """One of the section 6 ablations ('abs_unchecked' or 'rel_libm'); same
     buffers and return value as quantize().  Not error-bounded by design."""
-    import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA tensor")
     dt = _dtype_code(x.dtype)
     n = x.numel()
     k = _abl(kind)
     if out is None:
-        out = _empty(int(_lib.lcq_max_stream_bytes(dt, n)), torch.uint8, x.device, stream)
+        out = _empty(int(_lib.lcq_max_stream_bytes(dt, n)), _torch.uint8, x.device, stream)
     if nbytes is None:
-        nbytes = _empty(1, torch.int64, x.device, stream)
+        nbytes = _empty(1, _torch.int64, x.device, stream)
     if ws is None:
         base = ABS if k == ABL_ABS_UNCHECKED else REL
-        ws = _empty(int(_lib.lcq_workspace_bytes(base, dt, n)), torch.uint8, x.device, stream)
+        ws = _empty(int(_lib.lcq_workspace_bytes(base, dt, n)), _torch.uint8, x.device, stream)
     st = _lib.lcq_quantize_ablation(k, dt, float(eb), _ptr(x) if n else None, n, _ptr(out),
                                     out.numel(), _ptr(nbytes), _ptr(ws), ws.numel(),
                                     _stream_handle(stream))
@@ -236,12 +255,11 @@ def quantize_ablation(x, kind, eb, *, out=None, nbytes=None, ws=None, stream=Non
 def dequantize_ablation(stream_buf, kind, dtype, n, *, stream_bytes=None, out=None, ws=None,
                         stream=None):
     """Decode a stream of the given ablation kind (header status in ws)."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
         out = _empty(n, dtype, stream_buf.device, stream)
     if ws is None:
-        ws = _empty(64, torch.uint8, stream_buf.device, stream)
+        ws = _empty(64, _torch.uint8, stream_buf.device, stream)
     sb = stream_buf.numel() if stream_bytes is None else int(stream_bytes)
     st = _lib.lcq_dequantize_ablation(_abl(kind), dt, _ptr(stream_buf), sb, _ptr(out) if n else None,
                                       n, _ptr(ws), ws.numel(), _stream_handle(stream))
@@ -261,14 +279,13 @@ def pack(stream_buf, dtype, n, *, stream_bytes=None, out=None, nbytes=None, ws=N
     """Lossless packing stage: LCQ1 stream (uint8 CUDA tensor) -> packed
     stream.  Returns (packed buffer, one-element int64 tensor with its size);
     the input check's status lands in ws (read with stream_status)."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
-        out = _empty(pack_max_bytes(dtype, n), torch.uint8, stream_buf.device, stream)
+        out = _empty(pack_max_bytes(dtype, n), _torch.uint8, stream_buf.device, stream)
     if nbytes is None:
-        nbytes = _empty(1, torch.int64, stream_buf.device, stream)
+        nbytes = _empty(1, _torch.int64, stream_buf.device, stream)
     if ws is None:
-        ws = _empty(pack_workspace_bytes(dtype, n), torch.uint8, stream_buf.device, stream)
+        ws = _empty(pack_workspace_bytes(dtype, n), _torch.uint8, stream_buf.device, stream)
     sb = stream_buf.numel() if stream_bytes is None else int(stream_bytes)
     st = _lib.lcq_pack(dt, _ptr(stream_buf), sb, n, _ptr(out), out.numel(), _ptr(nbytes),
                        _ptr(ws), ws.numel(), _stream_handle(stream))
@@ -278,14 +295,13 @@ def pack(stream_buf, dtype, n, *, stream_bytes=None, out=None, nbytes=None, ws=N
 
 def unpack(packed_buf, dtype, n, *, packed_bytes=None, out=None, nbytes=None, ws=None, stream=None):
     """Inverse of pack(): (LCQ1 stream buffer, size tensor)."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
-        out = _empty(max_stream_bytes(dtype, n), torch.uint8, packed_buf.device, stream)
+        out = _empty(max_stream_bytes(dtype, n), _torch.uint8, packed_buf.device, stream)
     if nbytes is None:
-        nbytes = _empty(1, torch.int64, packed_buf.device, stream)
+        nbytes = _empty(1, _torch.int64, packed_buf.device, stream)
     if ws is None:
-        ws = _empty(64, torch.uint8, packed_buf.device, stream)
+        ws = _empty(64, _torch.uint8, packed_buf.device, stream)
     pb = packed_buf.numel() if packed_bytes is None else int(packed_bytes)
     st = _lib.lcq_unpack(dt, _ptr(packed_buf), pb, n, _ptr(out), out.numel(), _ptr(nbytes),
                          _ptr(ws), ws.numel(), _stream_handle(stream))
@@ -302,17 +318,16 @@ def compress(x, q, eb, *, out=None, nbytes=None, ws=None, stream=None):
     pack(quantize(x)), the codes never written to memory.  Returns (packed,
     nbytes): a uint8 device tensor of capacity pack_max_bytes and a
     one-element int64 device tensor receiving the packed size."""
-    import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA tensor")
     dt = _dtype_code(x.dtype)
     n = x.numel()
     if out is None:
-        out = _empty(int(_lib.lcq_pack_max_bytes(dt, n)), torch.uint8, x.device, stream)
+        out = _empty(int(_lib.lcq_pack_max_bytes(dt, n)), _torch.uint8, x.device, stream)
     if nbytes is None:
-        nbytes = _empty(1, torch.int64, x.device, stream)
+        nbytes = _empty(1, _torch.int64, x.device, stream)
     if ws is None:
-        ws = _empty(compress_workspace_bytes(q, x.dtype, n), torch.uint8, x.device, stream)
+        ws = _empty(compress_workspace_bytes(q, x.dtype, n), _torch.uint8, x.device, stream)
     st = _lib.lcq_compress(_q(q), dt, float(eb), _ptr(x) if n else None, n, _ptr(out),
                            out.numel(), _ptr(nbytes), _ptr(ws), ws.numel(), _stream_handle(stream))
     _check(st, "lcq_compress")
@@ -323,12 +338,11 @@ def decompress(packed, dtype, n, *, packed_bytes=None, out=None, ws=None, stream
     """Decode a packed stream straight to n values (lcq_decompress): the
     values of dequantize(unpack(packed)).  The device checks land in ws (read
     them with stream_status); packed_bytes defaults to the tensor's size."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
         out = _empty(n, dtype, packed.device, stream)
     if ws is None:
-        ws = _empty(64, torch.uint8, packed.device, stream)
+        ws = _empty(64, _torch.uint8, packed.device, stream)
     pb = packed.numel() if packed_bytes is None else int(packed_bytes)
     st = _lib.lcq_decompress(dt, _ptr(packed), pb, _ptr(out) if n else None, n, _ptr(ws),
                              ws.numel(), _stream_handle(stream))
@@ -348,15 +362,14 @@ def quantize_inline(x, q, eb, *, out=None, ws=None, stream=None):
     """Quantize x into the in-line layout (one word per value plus a bitmap
     of values stored raw).  Returns the stream, a uint8 device tensor of
     exactly inline_stream_bytes(x.dtype, x.numel()) bytes."""
-    import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA tensor")
     dt = _dtype_code(x.dtype)
     n = x.numel()
     if out is None:
-        out = _empty(int(_lib.lcq_inline_stream_bytes(dt, n)), torch.uint8, x.device, stream)
+        out = _empty(int(_lib.lcq_inline_stream_bytes(dt, n)), _torch.uint8, x.device, stream)
     if ws is None:
-        ws = _empty(int(_lib.lcq_inline_workspace_bytes(_q(q))), torch.uint8, x.device, stream)
+        ws = _empty(int(_lib.lcq_inline_workspace_bytes(_q(q))), _torch.uint8, x.device, stream)
     st = _lib.lcq_quantize_inline(_q(q), dt, float(eb), _ptr(x) if n else None, n, _ptr(out),
                                   out.numel(), _ptr(ws), ws.numel(), _stream_handle(stream))
     _check(st, "lcq_quantize_inline")
@@ -366,12 +379,11 @@ def quantize_inline(x, q, eb, *, out=None, ws=None, stream=None):
 def dequantize_inline(stream_buf, dtype, n, *, out=None, ws=None, stream=None):
     """Decode an in-line layout stream into n values; the header check's
     result lands in ws (read with stream_status)."""
-    import torch
     dt = _dtype_code(dtype)
     if out is None:
         out = _empty(n, dtype, stream_buf.device, stream)
     if ws is None:
-        ws = _empty(64, torch.uint8, stream_buf.device, stream)
+        ws = _empty(64, _torch.uint8, stream_buf.device, stream)
     st = _lib.lcq_dequantize_inline(dt, _ptr(stream_buf), stream_buf.numel(),
                                     _ptr(out) if n else None, n, _ptr(ws), ws.numel(),
                                     _stream_handle(stream))
