@@ -8,13 +8,15 @@
 //
 // Kernels (one wavefront per chunk, the chunk-per-wavefront mapping; full
 // chunks take code paths without per-position masks):
-//   k_pack_plan   widths, modes and record sizes; one atomic add per
-//                 workgroup into its group's byte count
-//   k_pack_scan   one workgroup per group: record offsets, header, padding,
-//                 packed size
+//   k_pack_plan   widths, modes and record sizes; per workgroup its record
+//                 bytes, or (large streams) an atomic add into its group's
+//                 byte count
+//   k_pack_scan   large streams only, one workgroup per group: record offsets,
+//                 header, padding, packed size
 //   k_pack_write  records (each chunk's packed bits assembled in LDS by
 //                 atomic ORs and stored 128 bits at a time), chunk table,
-//                 outliers
+//                 outliers; up to kMaxPackDirect plan workgroups, also the
+//                 offsets and the header
 //   k_unpack      per chunk: the whole record staged in LDS, record checks,
 //                 bit extraction, inverse zigzag, wavefront prefix sum
 //                 (delta mode), sentinels from the bitmap; header, chunk
@@ -121,6 +123,12 @@ __device__ __forceinline__ void write_chunk_record(const int32_t *codes, uint64_
              lane);
 }
 
+// Up to this many plan workgroups (of kStageWaves chunks; 16.7 M values) the
+// write pass finds its own offsets from their byte counts, 8 KiB read from L2
+// by each of its workgroups: no clear kernel before and no scan kernel
+// between (a 1 M value stream: 5 launches to pack and unpack become 3).
+constexpr unsigned kMaxPackDirect = 2048;
+
 struct PackArgs {
   const uint8_t *in;      // LCQ1 stream
   uint64_t in_bytes;
@@ -129,12 +137,32 @@ struct PackArgs {
   uint64_t *out_bytes;
   uint32_t *sizes;        // record bytes per chunk
   uint32_t *meta;         // w | mode << 8 | hb << 16 per chunk
-  unsigned long long *group;
+  uint32_t *totals;           // record bytes per plan workgroup, or null:
+  unsigned long long *group;  // record bytes per group
+  uint64_t ptiles;            // plan workgroups
   uint64_t tiles_per_group, chunks_per_group, ngroups;
   unsigned long long *status;
   uint64_t epoch;
   int dtype;
 };
+
+// Header, padding and size of the packed stream (k outliers), by one thread.
+__device__ __forceinline__ void finish_pack(const PackArgs &a, uint64_t payload, uint64_t k) {
+  const uint64_t nch = n_chunks(a.n);
+  const uint64_t ot = packed_table_offset(nch), pl = packed_payload_offset(nch);
+  const uint64_t s = a.dtype == LCQ_F64 ? 8 : 4;
+  const uint64_t oo = align16(pl + payload);
+  reinterpret_cast<uint64_t *>(a.out + ot)[nch] = payload;
+  const uint64_t *hin = reinterpret_cast<const uint64_t *>(a.in);
+  uint64_t *hout = reinterpret_cast<uint64_t *>(a.out);
+  hout[0] = (hin[0] & ~0xFFFFFFFFull) | kMagicPacked;
+#pragma unroll
+  for (int i = 1; i < 8; i++) hout[i] = hin[i];
+  for (uint64_t x = 64 + 8 * nch; x < ot; x++) a.out[x] = 0;
+  for (uint64_t x = ot + 8 * (nch + 1); x < pl; x++) a.out[x] = 0;
+  for (uint64_t x = pl + payload; x < oo; x++) a.out[x] = 0;
+  *a.out_bytes = oo + k * s;
+}
 
 __global__ __launch_bounds__(64 * kStageWaves) void k_pack_plan(PackArgs a) {
   __shared__ unsigned s_tot[kStageWaves];
@@ -157,10 +185,11 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_pack_plan(PackArgs a) {
   if (lane == 0) s_tot[wave] = size;
   __syncthreads();
   if (threadIdx.x == 0) {
-    unsigned long long t = 0;
+    unsigned t = 0;
 #pragma unroll
     for (int i = 0; i < kStageWaves; i++) t += s_tot[i];
-    if (t) atomicAdd(a.group + blockIdx.x / a.tiles_per_group, t);
+    if (a.totals) a.totals[blockIdx.x] = t;
+    else if (t) atomicAdd(a.group + blockIdx.x / a.tiles_per_group, (unsigned long long)t);
   }
 }
 
@@ -209,37 +238,85 @@ __global__ __launch_bounds__(kBlock) void k_pack_scan(PackArgs a) {
     __syncthreads();  // s_wt is rewritten by the next batch
   }
 
-  if (g == a.ngroups - 1 && tid == 0) {
-    const uint64_t s = a.dtype == LCQ_F64 ? 8 : 4;
-    const uint64_t oo = align16(pl + run);
-    offs[nch] = run;
-    const uint64_t *hin = reinterpret_cast<const uint64_t *>(a.in);
-    uint64_t *hout = reinterpret_cast<uint64_t *>(a.out);
-    hout[0] = (hin[0] & ~0xFFFFFFFFull) | kMagicPacked;
-#pragma unroll
-    for (int i = 1; i < 8; i++) hout[i] = hin[i];
-    for (uint64_t x = 64 + 8 * nch; x < ot; x++) a.out[x] = 0;
-    for (uint64_t x = ot + 8 * (nch + 1); x < pl; x++) a.out[x] = 0;
-    for (uint64_t x = pl + run; x < oo; x++) a.out[x] = 0;
-    *a.out_bytes = oo + k * s;
-  }
+  if (g == a.ngroups - 1 && tid == 0) finish_pack(a, run, k);
 }
 
+// Record bytes of the plan workgroups before `tile` and of all, to every
+// thread of the workgroup (a.totals; below 2^27 bytes, so 32 bits hold them).
+__device__ __forceinline__ void sum_pack_totals(const PackArgs &a, unsigned tile, uint32_t &before,
+                                                uint32_t &all) {
+  __shared__ uint32_t s_sum[2][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(kMaxPackDirect == 8 * kBlock, "two loads of four per thread");
+  const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(a.totals);
+  const unsigned nt = (unsigned)a.ptiles;
+  uint32_t vb = 0, va = 0;
+#pragma unroll
+  for (int r = 0; r < 2; r++) {
+    const unsigned i = (unsigned)(tid + r * kBlock);
+    const nt_i4 q = tot[4 * i < nt ? i : 0];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const unsigned t = 4 * i + u;
+      const uint32_t w = t < nt ? (uint32_t)q[u] : 0u;  // (words past the last are garbage)
+      vb += t < tile ? w : 0u;
+      va += w;
+    }
+  }
+  vb = lane63(wave_incl_add(vb));
+  va = lane63(wave_incl_add(va));
+  if (lane == 0) {
+    s_sum[0][wave] = vb;
+    s_sum[1][wave] = va;
+  }
+  __syncthreads();
+  before = all = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; w++) {
+    before += s_sum[0][w];
+    all += s_sum[1][w];
+  }
+}
+static_assert((uint64_t)kMaxPackDirect * kStageWaves * kMaxRecord < (1ull << 32), "32-bit sums");
+
 // Records, chunk table and outliers.  Each chunk's packed bits are
-// assembled in LDS (pack_bits) and leave in 128-bit stores.
+// assembled in LDS (pack_bits) and leave in 128-bit stores.  DIRECT: offsets
+// from the totals (no scan kernel ran), header, size and status too.
+template <bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_pack_write(PackArgs a) {
   __shared__ uint32_t s_w[kWaves][kChunk];  // each wavefront's packed words
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t n = a.n, nch = n_chunks(n);
   uint64_t k;
-  if (!lcq1_header_ok(a.in, a.in_bytes, a.dtype, n, k)) return;  // uniform over the grid
+  const bool ok = lcq1_header_ok(a.in, a.in_bytes, a.dtype, n, k);  // uniform over the grid
+  if (!ok) {
+    if (DIRECT && blockIdx.x == 0 && threadIdx.x == 0)
+      report_status(a.status, a.epoch << 16, LCQ_ERR_STREAM);
+    return;
+  }
   const uint64_t ot = packed_table_offset(nch), pl = packed_payload_offset(nch);
   const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
+  uint64_t *offs = reinterpret_cast<uint64_t *>(a.out + ot);
+  uint64_t off = 0, payload;
+  if constexpr (DIRECT) {
+    const unsigned tile = (unsigned)(blockIdx.x * kWaves / kStageWaves);
+    static_assert(kStageWaves % kWaves == 0, "a write workgroup lies in one plan workgroup");
+    uint32_t before, all;
+    sum_pack_totals(a, tile, before, all);
+    off = before;
+    payload = all;
+    for (uint64_t i = (uint64_t)tile * kStageWaves; i < c && i < nch; i++) off += a.sizes[i];
+    if (c < nch && lane == 0) offs[c] = off;
+    if (c == nch - 1 && lane == 0) finish_pack(a, payload, k);
+  } else {
+    payload = offs[nch];
+    if (c < nch) off = offs[c];
+  }
   if (c < nch) {  // uniform over the wavefront
     const int32_t *codes = reinterpret_cast<const int32_t *>(a.in + 64);
     const uint32_t m = a.meta[c];
-    uint8_t *rec = a.out + pl + reinterpret_cast<const uint64_t *>(a.out + ot)[c];
+    uint8_t *rec = a.out + pl + off;
     if (chunk_len(n, c) == kChunk) write_chunk_record<true>(codes, n, c, lane, m, s_w[wave], rec);
     else write_chunk_record<false>(codes, n, c, lane, m, s_w[wave], rec);
     if (lane == 0) {
@@ -249,7 +326,6 @@ __global__ __launch_bounds__(kBlock) void k_pack_write(PackArgs a) {
   }
   // outliers, grid-stride over the raw words
   const uint64_t s = a.dtype == LCQ_F64 ? 8 : 4;
-  const uint64_t payload = reinterpret_cast<const uint64_t *>(a.out + ot)[nch];
   const uint64_t oo = align16(pl + payload);
   const uint64_t words = k * s / 4;
   const uint32_t *src = reinterpret_cast<const uint32_t *>(a.in + outlier_offset(n));
@@ -257,6 +333,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_write(PackArgs a) {
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words;
        i += (uint64_t)gridDim.x * kBlock)
     dst[i] = src[i];
+  if (DIRECT && blockIdx.x == 0 && threadIdx.x == 0) report_status(a.status, a.epoch << 16, LCQ_OK);
 }
 
 struct UnpackArgs {
@@ -422,13 +499,22 @@ lcq_status lcq_pack(lcq_dtype t, const void *d_stream, uint64_t stream_bytes, ui
   a.status = reinterpret_cast<unsigned long long *>(ws);
   a.epoch = g_pk_epoch.fetch_add(1) + 1;
   a.dtype = (int)t;
+  a.ptiles = ptiles;
+  if (ptiles && ptiles <= kMaxPackDirect) {
+    static_assert(4 * kMaxPackDirect <= 8 * kMaxGroups, "the totals take the group sums' place");
+    a.totals = reinterpret_cast<uint32_t *>(a.group);
+    hipLaunchKernelGGL(k_pack_plan, dim3((unsigned)ptiles), dim3(64 * kStageWaves), 0, stream, a);
+    hipLaunchKernelGGL(k_pack_write<true>, dim3((unsigned)ntiles), dim3(kBlock), 0, stream, a);
+    return check_launch_pk();
+  }
   const unsigned cg = (unsigned)std::min<uint64_t>((a.ngroups + kBlock - 1) / kBlock, 1024);
   hipLaunchKernelGGL(k_clear_pk, dim3(cg), dim3(kBlock), 0, stream,
                      reinterpret_cast<uint64_t *>(a.group), a.ngroups);
   if (ntiles)
     hipLaunchKernelGGL(k_pack_plan, dim3((unsigned)ptiles), dim3(64 * kStageWaves), 0, stream, a);
   hipLaunchKernelGGL(k_pack_scan, dim3((unsigned)a.ngroups), dim3(kBlock), 0, stream, a);
-  if (ntiles) hipLaunchKernelGGL(k_pack_write, dim3((unsigned)ntiles), dim3(kBlock), 0, stream, a);
+  if (ntiles)
+    hipLaunchKernelGGL(k_pack_write<false>, dim3((unsigned)ntiles), dim3(kBlock), 0, stream, a);
   return check_launch_pk();
 }
 
