@@ -135,7 +135,10 @@ struct StageQ {
   uint32_t *totals;           // one per pass-1 workgroup, or null:
   unsigned long long *group;  // one per group
   uint64_t tiles_per_group, chunks_per_group, ngroups;
-  const DevParams *noa;
+  DevParams *noa;
+  const void *partials;  // NOA, nparts > 0: range pairs pass 1 still has to reduce
+  unsigned nparts;
+  uint64_t eb_down;
   uint64_t step, inv, bound, low;  // ABS / REL parameters (raw bits)
   uint64_t hdr[8];
 };
@@ -153,7 +156,8 @@ __device__ __forceinline__ FieldParams<T> stage_params(const StageQ &a) {
   return p;
 }
 
-template <typename T, int Q, int CPW, int PF>
+// FOLD (NOA): the parameters from the range pairs.
+template <typename T, int Q, int CPW, int PF, bool FOLD = false>
 __global__ __launch_bounds__(64 * stage_waves<T>()) void k_quant_stage(StageQ a) {
   using U = typename FT<T>::U;
   StageField<T> f;
@@ -165,7 +169,11 @@ __global__ __launch_bounds__(64 * stage_waves<T>()) void k_quant_stage(StageQ a)
   f.totals = a.totals;
   f.group = a.group;
   f.tiles_per_group = a.tiles_per_group;
-  f.p = stage_params<T, Q>(a);
+  if constexpr (FOLD)
+    f.p = params_from<T>(fold_params<T>(static_cast<const T *>(a.partials), a.nparts,
+                                        from_bits((U)a.eb_down), a.noa));
+  else
+    f.p = stage_params<T, Q>(a);
   quant_chunks<T, Q, CPW, PF>(f, blockIdx.x);
 }
 
@@ -365,8 +373,12 @@ template <typename T, int Q, int V>
 void launch_quantize(const PlainQ &a, const StageQ &sq, hipStream_t s) {
   constexpr QShape sh = kQVariants[V];
   if constexpr (sh.cpw > 0) {
-    hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf>), dim3((unsigned)a.ntiles),
-                       dim3(64 * stage_waves<T>()), 0, s, sq);
+    if (Q == kNOA && sq.nparts)
+      hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf, Q == kNOA>), dim3((unsigned)a.ntiles),
+                         dim3(64 * stage_waves<T>()), 0, s, sq);
+    else
+      hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf>), dim3((unsigned)a.ntiles),
+                         dim3(64 * stage_waves<T>()), 0, s, sq);
     if (g_ev_mid) (void)hipEventRecord(g_ev_mid, s);
     hipLaunchKernelGGL((k_quant_finish<T, Q>), dim3((unsigned)sq.ngroups), dim3(kBlock), 0, s,
                        sq);
@@ -484,7 +496,7 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
     }
     sq.chunks_per_group = sq.tiles_per_group * (tile / kChunk);
     sq.ngroups = (a.ntiles + sq.tiles_per_group - 1) / sq.tiles_per_group;
-    sq.noa = a.noa;
+    sq.noa = reinterpret_cast<DevParams *>(ws + kWsParams);
     sq.step = a.step;
     sq.inv = a.inv;
     sq.bound = a.bound;
@@ -496,9 +508,11 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
 
   if (Q == kNOA) {
     T *partials = reinterpret_cast<T *>(ws + ws_partials_off((lcq_dtype)dt, n));
-    launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr, clear_count,
-                        from_bits((typename FT<T>::U)hp.eb_down),
-                        reinterpret_cast<DevParams *>(ws + kWsParams), s);
+    sq.partials = partials;
+    sq.eb_down = hp.eb_down;
+    sq.nparts = launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr,
+                                    clear_count, from_bits((typename FT<T>::U)hp.eb_down),
+                                    reinterpret_cast<DevParams *>(ws + kWsParams), s, staged && n);
   } else if (clear_count) {
     const unsigned nb = (unsigned)std::min<uint64_t>((clear_count + kBlock - 1) / kBlock, 1024);
     hipLaunchKernelGGL(k_clear, dim3(nb), dim3(kBlock), 0, s, clear_ptr, clear_count);

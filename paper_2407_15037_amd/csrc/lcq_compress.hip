@@ -74,7 +74,10 @@ struct CmpArgs {
   unsigned long long *rgroup;  // record bytes per group
   uint64_t ntiles;
   uint64_t tiles_per_group, chunks_per_group, ngroups;
-  const DevParams *noa;        // NOA: parameters computed on the device
+  DevParams *noa;              // NOA: parameters computed on the device
+  const void *partials;        // NOA, nparts > 0: range pairs pass 1 still has to reduce
+  unsigned nparts;
+  uint64_t eb_down;
   uint64_t step, inv, bound, low;  // ABS / REL parameters (raw bits)
   uint64_t hdr[8];                 // header of the packed stream
 };
@@ -175,14 +178,20 @@ __device__ __forceinline__ void load_chunk_cached(const T *in, uint64_t n, uint6
 // cost more occupancy than the extra loads in flight gain.  float32 is held to
 // 64 registers, 8 wavefronts per SIMD: 227 to 221 us; float64 at 7 or 8 per
 // SIMD spills, 196 to 216 us REL, and is left to the compiler.)
-template <typename T, int Q>
+// FOLD (NOA): the parameters from the range pairs.
+template <typename T, int Q, bool FOLD>
 __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 8 : 1) void k_cmp_stage(CmpArgs a) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
   __shared__ unsigned s_cnt[kWaves], s_rb[kWaves];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk logic is scalar
   const uint64_t n = a.n, nch = n_chunks(n);
-  const FieldParams<T> p = cmp_params<T, Q>(a);
+  FieldParams<T> p;
+  if constexpr (FOLD)
+    p = params_from<T>(fold_params<T>(static_cast<const T *>(a.partials), a.nparts,
+                                      from_bits((typename FT<T>::U)a.eb_down), a.noa));
+  else
+    p = cmp_params<T, Q>(a);
   const EncK<T> k = enc_consts_pinned<T, Q>(p);
   unsigned cnt = 0, rb = 0;
   const uint64_t c = (uint64_t)blockIdx.x * kWaves + wave;
@@ -642,7 +651,7 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   a.tiles_per_group = tiles_per_group(ntiles, kWaves);
   a.chunks_per_group = a.tiles_per_group * kWaves;
   a.ngroups = std::max<uint64_t>(1, (ntiles + a.tiles_per_group - 1) / a.tiles_per_group);
-  a.noa = reinterpret_cast<const DevParams *>(ws + kCwParams);
+  a.noa = reinterpret_cast<DevParams *>(ws + kCwParams);
   a.step = hp.step;
   a.inv = hp.inv;
   a.bound = hp.bound;
@@ -659,15 +668,19 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   const uint64_t clear_count = a.totals ? 0 : 2 * kMaxGroups;
   if (Q == kNOA) {
     T *partials = reinterpret_cast<T *>(ws + cw_partials_off((lcq_dtype)dt, C));
-    launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr, clear_count,
-                        from_bits((typename FT<T>::U)hp.eb_down),
-                        reinterpret_cast<DevParams *>(ws + kCwParams), s);
+    a.partials = partials;
+    a.eb_down = hp.eb_down;
+    a.nparts = launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr,
+                                   clear_count, from_bits((typename FT<T>::U)hp.eb_down), a.noa, s,
+                                   n != 0);
   } else if (clear_count) {
     hipLaunchKernelGGL(k_clear_cmp, dim3((unsigned)(clear_count / kBlock)), dim3(kBlock), 0, s,
                        clear_ptr, clear_count);
   }
-  if (ntiles)
-    hipLaunchKernelGGL((k_cmp_stage<T, Q>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  if (Q == kNOA && a.nparts)
+    hipLaunchKernelGGL((k_cmp_stage<T, Q, Q == kNOA>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  else if (ntiles)
+    hipLaunchKernelGGL((k_cmp_stage<T, Q, false>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
   if (a.totals) {
     hipLaunchKernelGGL((k_cmp_write<T, Q, true>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
   } else {

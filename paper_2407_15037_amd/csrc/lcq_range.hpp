@@ -9,6 +9,12 @@
 
 namespace lcq {
 constexpr int kMinmaxBlocks = 8192;  // range workgroups at most
+// Up to this many range workgroups (4 M float32 values) the next kernel's
+// wavefronts reduce the per-workgroup results themselves (8 pairs per lane,
+// while their chunk's values are on the way): the one-workgroup parameter
+// kernel between, 2 us and a launch, is left out.  Beyond, each workgroup
+// would read more than it saves.
+constexpr unsigned kFoldBlocks = 512;
 }  // namespace lcq
 
 namespace {
@@ -77,12 +83,51 @@ __global__ __launch_bounds__(kBlock) void k_noa_params(const T *partials, int np
   *out = noa_params<T>(lo, hi, eb_down);
 }
 
+// The same by every wavefront of a consuming kernel (nparts <= kFoldBlocks;
+// uniform result); one workgroup of the grid leaves it at `out` for the
+// kernels after.
+template <typename T>
+__device__ __forceinline__ DevParams fold_params(const T *partials, unsigned nparts, T eb_down,
+                                                 DevParams *out) {
+  const unsigned lane = threadIdx.x & 63;
+  T l[kFoldBlocks / 64], h[kFoldBlocks / 64];
+#pragma unroll
+  for (unsigned k = 0; k < kFoldBlocks / 64; k++) {  // all in flight, clamped
+    const unsigned i = min(lane + 64 * k, nparts - 1);
+    l[k] = partials[2 * i];
+    h[k] = partials[2 * i + 1];
+  }
+  T lo = l[0], hi = h[0];
+#pragma unroll
+  for (unsigned k = 1; k < kFoldBlocks / 64; k++) {
+    lo = fmin(lo, l[k]);
+    hi = fmax(hi, h[k]);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o, 64));
+    hi = fmax(hi, __shfl_xor(hi, o, 64));
+  }
+  DevParams d = noa_params<T>(lo, hi, eb_down);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *out = d;
+  // into scalar registers: every lane holds the same values
+  uint32_t w[sizeof(DevParams) / 4];
+  __builtin_memcpy(w, &d, sizeof d);
+#pragma unroll
+  for (unsigned k = 0; k < sizeof(DevParams) / 4; k++) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+  __builtin_memcpy(&d, w, sizeof d);
+  return d;
+}
+
 // Range pass of n values at d_in: per-workgroup (min, max) pairs into
 // partials (2 * kMinmaxBlocks values of T), then the field's parameters into
-// *out; the first kernel also zeroes clear[0..clear_count).
+// *out; the first kernel also zeroes clear[0..clear_count).  fold: the caller's
+// next kernel may take the parameters with fold_params; returns the number of
+// pairs if it has to, else 0.
 template <typename T>
-void launch_noa_range(const T *d_in, uint64_t n, T *partials, uint64_t *clear,
-                      uint64_t clear_count, T eb_down, DevParams *out, hipStream_t s) {
+unsigned launch_noa_range(const T *d_in, uint64_t n, T *partials, uint64_t *clear,
+                      uint64_t clear_count, T eb_down, DevParams *out, hipStream_t s,
+                          bool fold = false) {
   // each workgroup reduces a contiguous share of whole 128-bit vectors
   const uint64_t W = 16 / sizeof(T);
   const uint64_t per = (uint64_t)kBlock * W * 8;  // >= 8 vectors per thread
@@ -92,8 +137,10 @@ void launch_noa_range(const T *d_in, uint64_t n, T *partials, uint64_t *clear,
   share = (share + W - 1) / W * W;
   hipLaunchKernelGGL(k_minmax<T>, dim3((unsigned)nb), dim3(kBlock), 0, s, d_in, n, share,
                      partials, clear, clear_count);
+  if (fold && nb <= kFoldBlocks) return (unsigned)nb;
   hipLaunchKernelGGL(k_noa_params<T>, dim3(1), dim3(kBlock), 0, s, partials, (int)nb, eb_down,
                      out);
+  return 0;
 }
 
 }  // namespace

@@ -83,3 +83,36 @@ def test_compress_totals_limit(dt, n):
     pk, nb = lcq.compress(xt, "abs", 1e-3, out=out, ws=ws)
     want = O.pack(O.quantize_mt("abs", x, 1e-3), dt, n)
     assert first_diff(pk[: int(nb.item())].cpu().numpy(), want) is None
+
+
+# NOA: 512 range workgroups of 8192 float32 / 4096 float64 values, and one more
+@pytest.mark.parametrize("dt,n", [(np.float32, 512 * 8192), (np.float32, 512 * 8192 + 1),
+                                  (np.float64, 512 * 4096), (np.float64, 512 * 4096 + 1),
+                                  (np.float32, 64 * 8192 + 1)])
+def test_noa_fold_limit(dt, n):
+    import torch
+    import paper_2407_15037_amd as lcq
+    x = synth.with_specials(synth.sines_1d(n, 13, dtype=dt), "noa", n // 500, 5, 1e-3)
+    x[-1] = dt(3.0) * np.abs(x[np.isfinite(x)]).max()  # the range ends in the last workgroup
+    announce("noa fold limit", np.dtype(dt).name, n)
+    st = O.quantize_mt("noa", x, 1e-3)
+    assert first_diff(_gpu_stream("noa", x, 1e-3), st) is None
+    pk, nb = lcq.compress(torch.from_numpy(x).cuda(), "noa", 1e-3)
+    assert first_diff(pk[: int(nb.item())].cpu().numpy(), O.pack(st, dt, n)) is None
+
+
+# pack: 2048 plan workgroups of 8 chunks, and one more; a small ragged one
+@pytest.mark.parametrize("n", [1, 4 * 1024 + 1, 8 * 1024 + 1, 2048 * 8 * 1024, 2048 * 8 * 1024 + 1])
+def test_pack_totals_limit(n):
+    import torch
+    import paper_2407_15037_amd as lcq
+    x = synth.sines_1d(n, 14, dtype=np.float32)
+    x[::977] = np.nan
+    st = O.quantize_mt("abs", x, 1e-3)
+    announce("pack totals limit", n)
+    ws = torch.full((lcq.pack_workspace_bytes(torch.float32, n),), 0xA5, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((lcq.pack_max_bytes(torch.float32, n),), 0x5A, dtype=torch.uint8, device="cuda")
+    pk, nb = lcq.pack(torch.from_numpy(st).cuda(), torch.float32, n, out=out, ws=ws)
+    assert lcq.stream_status(ws) == lcq.OK
+    assert first_diff(pk[: int(nb.item())].cpu().numpy(), O.pack(st, np.float32, n)) is None
