@@ -156,8 +156,7 @@ __device__ __forceinline__ FieldParams<T> stage_params(const StageQ &a) {
   return p;
 }
 
-// FOLD (NOA): the parameters from the range pairs.
-template <typename T, int Q, int CPW, int PF, bool FOLD = false>
+template <typename T, int Q, int CPW, int PF>
 __global__ __launch_bounds__(64 * stage_waves<T>()) void k_quant_stage(StageQ a) {
   using U = typename FT<T>::U;
   StageField<T> f;
@@ -169,7 +168,7 @@ __global__ __launch_bounds__(64 * stage_waves<T>()) void k_quant_stage(StageQ a)
   f.totals = a.totals;
   f.group = a.group;
   f.tiles_per_group = a.tiles_per_group;
-  if constexpr (FOLD)
+  if (Q == kNOA && a.nparts)  // (uniform)
     f.p = params_from<T>(fold_params<T>(static_cast<const T *>(a.partials), a.nparts,
                                         from_bits((U)a.eb_down), a.noa));
   else
@@ -373,12 +372,8 @@ template <typename T, int Q, int V>
 void launch_quantize(const PlainQ &a, const StageQ &sq, hipStream_t s) {
   constexpr QShape sh = kQVariants[V];
   if constexpr (sh.cpw > 0) {
-    if (Q == kNOA && sq.nparts)
-      hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf, Q == kNOA>), dim3((unsigned)a.ntiles),
-                         dim3(64 * stage_waves<T>()), 0, s, sq);
-    else
-      hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf>), dim3((unsigned)a.ntiles),
-                         dim3(64 * stage_waves<T>()), 0, s, sq);
+    hipLaunchKernelGGL((k_quant_stage<T, Q, sh.cpw, sh.pf>), dim3((unsigned)a.ntiles),
+                       dim3(64 * stage_waves<T>()), 0, s, sq);
     if (g_ev_mid) (void)hipEventRecord(g_ev_mid, s);
     hipLaunchKernelGGL((k_quant_finish<T, Q>), dim3((unsigned)sq.ngroups), dim3(kBlock), 0, s,
                        sq);

@@ -777,7 +777,7 @@ __device__ __forceinline__ void quant_small(const SmallField<T> &f) {
       }
     }
     block_range<T, kSmallWaves>(lo, hi, s_lo, s_hi);
-    d = noa_params<T>(lo, hi, f.eb_down);
+    d = noa_params<T, false>(uniform(lo), uniform(hi), f.eb_down);
     p = params_from<T>(d);
   } else {
     __syncthreads();  // s_cnt is zero

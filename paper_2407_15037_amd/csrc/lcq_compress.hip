@@ -178,8 +178,7 @@ __device__ __forceinline__ void load_chunk_cached(const T *in, uint64_t n, uint6
 // cost more occupancy than the extra loads in flight gain.  float32 is held to
 // 64 registers, 8 wavefronts per SIMD: 227 to 221 us; float64 at 7 or 8 per
 // SIMD spills, 196 to 216 us REL, and is left to the compiler.)
-// FOLD (NOA): the parameters from the range pairs.
-template <typename T, int Q, bool FOLD>
+template <typename T, int Q>
 __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 8 : 1) void k_cmp_stage(CmpArgs a) {
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
   __shared__ unsigned s_cnt[kWaves], s_rb[kWaves];
@@ -187,7 +186,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 8 : 1) void k_cmp_stage(Cm
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: chunk logic is scalar
   const uint64_t n = a.n, nch = n_chunks(n);
   FieldParams<T> p;
-  if constexpr (FOLD)
+  if (Q == kNOA && a.nparts)  // (uniform)
     p = params_from<T>(fold_params<T>(static_cast<const T *>(a.partials), a.nparts,
                                       from_bits((typename FT<T>::U)a.eb_down), a.noa));
   else
@@ -677,10 +676,8 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
     hipLaunchKernelGGL(k_clear_cmp, dim3((unsigned)(clear_count / kBlock)), dim3(kBlock), 0, s,
                        clear_ptr, clear_count);
   }
-  if (Q == kNOA && a.nparts)
-    hipLaunchKernelGGL((k_cmp_stage<T, Q, Q == kNOA>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
-  else if (ntiles)
-    hipLaunchKernelGGL((k_cmp_stage<T, Q, false>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
+  if (ntiles)
+    hipLaunchKernelGGL((k_cmp_stage<T, Q>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
   if (a.totals) {
     hipLaunchKernelGGL((k_cmp_write<T, Q, true>), dim3((unsigned)ntiles), dim3(kBlock), 0, s, a);
   } else {

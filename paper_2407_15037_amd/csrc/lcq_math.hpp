@@ -52,6 +52,58 @@ LCQ_HD double abs_t(double x) { return __builtin_fabs(x); }
 // largest finite value).
 template <typename T> LCQ_HD T step_down(T v) { return from_bits(to_bits(v) - 1); }
 
+// 1 / v for v > 0 (normal, subnormal or infinite), rounded to nearest even: the
+// value the division gives, by long division in integers.  For kernels that
+// encode values and derive their own parameters: the division's instruction
+// sequence is built on fused multiply-adds, which those kernels hold none of
+// (section 3.2; their instructions are checked).  On uniform operands it runs
+// in the scalar unit, 24 or 53 short steps.
+template <typename T> LCQ_HD T recip_rne(T v) {
+  using F = FT<T>;
+  using U = typename F::U;
+  constexpr int P = F::kMant + 1;  // significand bits
+  constexpr U kHidden = (U)1 << F::kMant;
+  const U u = to_bits(v);
+  const int ex = (int)(u >> F::kMant);
+  if (ex == (int)F::kExpMask) return (T)0;
+  U m = u & F::kFracMask;
+  int e;  // v = m 2^e, m in [2^(P-1), 2^P)
+  if (ex == 0) {
+    const int sh = (sizeof(T) == 4 ? __builtin_clz((unsigned)m)
+                                   : __builtin_clzll((unsigned long long)m)) -
+                   ((int)sizeof(T) * 8 - P);
+    m <<= sh;
+    e = 1 - F::kBias - F::kMant - sh;
+  } else {
+    m |= kHidden;
+    e = ex - F::kBias - F::kMant;
+  }
+  // q = floor(2^(2P) / m), P + 1 bits, and whether a remainder is left; the
+  // reciprocal's exponent is E
+  int E = -P - e;
+  U q = 1, rem = ((U)1 << P) - m;
+  if (m == kHidden) {  // a power of two
+    q = (U)1 << P;
+    rem = 0;
+    E++;
+  } else {
+    for (int i = 0; i < P; i++) {
+      rem <<= 1;
+      q <<= 1;
+      if (rem >= m) {
+        rem -= m;
+        q |= 1;
+      }
+    }
+  }
+  if (E > F::kBias) return from_bits((U)((U)F::kExpMask << F::kMant));
+  const int drop = 1 + (E < 1 - F::kBias ? 1 - F::kBias - E : 0);
+  U keep = q >> drop;
+  const U half = (U)1 << (drop - 1), rest = q & (((U)1 << drop) - 1);
+  if (rest > half || (rest == half && (rem != 0 || (keep & 1)))) keep++;
+  return from_bits(E < 1 - F::kBias ? keep : ((U)(E + F::kBias - 1) << F::kMant) + keep);
+}
+
 // Approximate log2 of section 3.2 (Mitchell): for |a| = 2^e (1 + m) it is
 // e + m, computed as the float 1.m plus the float (E - bias - 1), where E is
 // the biased exponent field.  The sign bit is ignored.

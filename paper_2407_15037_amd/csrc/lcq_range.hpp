@@ -108,14 +108,9 @@ __device__ __forceinline__ DevParams fold_params(const T *partials, unsigned npa
     lo = fmin(lo, __shfl_xor(lo, o, 64));
     hi = fmax(hi, __shfl_xor(hi, o, 64));
   }
-  DevParams d = noa_params<T>(lo, hi, eb_down);
+  // (every lane holds the same range: into scalar registers)
+  const DevParams d = noa_params<T, false>(uniform(lo), uniform(hi), eb_down);
   if (blockIdx.x == 0 && threadIdx.x == 0) *out = d;
-  // into scalar registers: every lane holds the same values
-  uint32_t w[sizeof(DevParams) / 4];
-  __builtin_memcpy(w, &d, sizeof d);
-#pragma unroll
-  for (unsigned k = 0; k < sizeof(DevParams) / 4; k++) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
-  __builtin_memcpy(&d, w, sizeof d);
   return d;
 }
 

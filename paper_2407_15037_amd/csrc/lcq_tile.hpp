@@ -99,6 +99,16 @@ __device__ __forceinline__ uint32_t lane63(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// A value every lane holds, in scalar registers.
+__device__ __forceinline__ float uniform(float v) {
+  return from_bits((uint32_t)__builtin_amdgcn_readfirstlane((int)to_bits(v)));
+}
+__device__ __forceinline__ double uniform(double v) {
+  const uint64_t u = to_bits(v);
+  return from_bits((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u) |
+                   ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32)) << 32));
+}
+
 __device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -601,8 +611,9 @@ __device__ void block_minmax(const T *in, uint64_t begin, uint64_t end, T &lo, T
 // NOA parameters from the finite range (section 2.1.3): R = hi - lo
 // (overflow clamped to the largest finite value), then ebR = RD(eb) * R with
 // each rounded step followed by one step toward zero, so ebR <= eb * R
-// exactly; no usable range -> every value lossless.
-template <typename T> __device__ DevParams noa_params(T lo, T hi, T eb_down) {
+// exactly; no usable range -> every value lossless.  DIV false: 1/step without
+// the division instruction sequence (recip_rne; lo and hi uniform).
+template <typename T, bool DIV = true> __device__ DevParams noa_params(T lo, T hi, T eb_down) {
   using U = typename FT<T>::U;
   const T tmax = from_bits((U)(((U)FT<T>::kExpMask << FT<T>::kMant) - 1));
   T r = hi - lo;
@@ -619,7 +630,7 @@ template <typename T> __device__ DevParams noa_params(T lo, T hi, T eb_down) {
     const T step = ebr + ebr;
     d.bound = to_bits(ebr);
     d.step = to_bits(step);
-    d.inv = to_bits((T)1 / step);
+    d.inv = to_bits(DIV ? (T)1 / step : recip_rne(step));
     d.lossless_all = 0;
   } else {
     d.bound = 0;

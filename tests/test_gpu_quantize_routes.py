@@ -116,3 +116,17 @@ def test_pack_totals_limit(n):
     pk, nb = lcq.pack(torch.from_numpy(st).cuda(), torch.float32, n, out=out, ws=ws)
     assert lcq.stream_status(ws) == lcq.OK
     assert first_diff(pk[: int(nb.item())].cpu().numpy(), O.pack(st, np.float32, n)) is None
+
+
+# bin widths from subnormal to near the largest value: their reciprocals
+# overflow, are subnormal, or round at the ends of the range
+@pytest.mark.parametrize("dt,exps", [(np.float32, (-37, -30, 0, 30, 38)),
+                                     (np.float64, (-306, -300, 0, 300, 308))])
+@pytest.mark.parametrize("n", [5000, 40000])
+def test_noa_scales(dt, exps, n):
+    for e in exps:
+        for eb in (0.3, 1e-2, 1e-7):
+            x = synth.sines_1d(n, 15, dtype=np.float64)
+            x = (x / np.abs(x).max() * 10.0 ** e).astype(dt)
+            announce("noa scales", np.dtype(dt).name, n, e, eb)
+            assert first_diff(_gpu_stream("noa", x, eb), O.quantize("noa", x, eb)) is None, (e, eb)
