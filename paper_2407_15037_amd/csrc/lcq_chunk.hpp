@@ -54,13 +54,14 @@ constexpr uint64_t kGroupChunks = 64;  // chunks per group at least (many fields
 // exceed the stage cap, kept 46 workgroups of 64 rescans each busy for 18 us.
 constexpr uint64_t kGroupChunksAlone = 16;
 // Up to this many pass-1 workgroups each stores its own outlier count and
-// pass 2 sums those of the earlier groups itself (8 KiB at most, two loads
+// pass 2 sums those of the earlier groups itself (16 KiB at most, four loads
 // per thread); above it the counts go to one atomic sum per group, which a
 // kernel of its own has to clear first.  The launch saved is a third of a
-// small field's; a large one does not show it (the clear runs in the shadow
-// of the operation before), and 16,384 totals summed by each of 1024 pass-2
+// small field's, and 1 us of a 16.7 M value one (4096 workgroups, ABS 31.7 to
+// 30.6 us); a large one does not show it (the clear runs in the shadow of the
+// operation before), and 16,384 totals summed by each of 1024 pass-2
 // workgroups cost more than the clear (512^3 float32 ABS 195 us against 191).
-constexpr uint64_t kMaxDirectTiles = 2048;
+constexpr uint64_t kMaxDirectTiles = 4096;
 
 // Pass-1 workgroups per pass-2 group for a field of `ntiles` pass-1
 // workgroups of `chunks_per_tile` chunks each: at least min_chunks chunks
@@ -287,12 +288,12 @@ __device__ __forceinline__ unsigned encode_chunk(const StageField<T> &f, uint64_
                                     : encode_chunk_at<T, Q, false>(f, c, lane, x, srow, k);
 }
 
-// Pass 1 for the CPW * stage_waves<T>() chunks of workgroup `tile`, PF chunks per
+// Pass 1 for the CPW * stage_waves<T, Q>() chunks of workgroup `tile`, PF chunks per
 // wavefront loaded before any is encoded.
 template <typename T, int Q, int CPW, int PF>
 __device__ void quant_chunks(const StageField<T> &f, uint64_t tile) {
   static_assert(PF > 0 && CPW % PF == 0, "whole prefetch groups");
-  constexpr int kSW = stage_waves<T>();
+  constexpr int kSW = stage_waves<T, Q>();
   constexpr int W = ChunkShape<T>::W, NSUB = ChunkShape<T>::NSUB;
   __shared__ unsigned s_cnt[kSW];
   __shared__ typename FT<T>::U s_stage[kSW][stage_cap<T>()];  // one row per wavefront
@@ -591,9 +592,9 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
     const unsigned m = (unsigned)(g * f.tiles_per_group / 4);
     unsigned t = 0;
-    static_assert(kMaxDirectTiles == 8 * kBlock, "two loads of four per thread");
+    static_assert(kMaxDirectTiles == 16 * kBlock, "four loads of four per thread");
 #pragma unroll
-    for (int k = 0; k < 2; k++) {
+    for (int k = 0; k < 4; k++) {
       const unsigned i = (unsigned)(tid + k * kBlock);
       const nt_i4 v = tot[i < m ? i : 0];
       const unsigned q = (unsigned)v.x + (unsigned)v.y + (unsigned)v.z + (unsigned)v.w;

@@ -20,15 +20,19 @@ namespace lcq {
 
 constexpr int kBlock = 256;  // threads per workgroup (4 wave64)
 constexpr int kWaves = kBlock / 64;
-// Wavefronts per workgroup of the quantize first pass (one chunk each),
-// per dtype: for float32, 8 halves its group-counter atomic adds against 4
-// (REL, with outliers in almost every chunk, adds on every workgroup):
-// measured quantize ABS 195 -> 188 us, REL 203 -> 199 us on the 512^3 field
-// (16: REL 249 us); for float64 (half the chunks per byte) 8 measured slower
-// than 4 on the 384^3 grid (ABS pass 1 109 -> 112 us), so it keeps 4.  The
-// pack plan takes 8 (kStageWaves).
+// Wavefronts per workgroup of the quantize first pass (one chunk each).
+// float32 REL, with outliers in almost every chunk of a field too large for
+// pass-1 totals, adds to its group's counter on every workgroup, and 8 halve
+// those adds: 188.7 us on the 512^3 field against 193.0 with 4 (16: 249).
+// float32 NOA, whose input the range pass left in the Infinity Cache up to
+// 256 MB, takes 8 as well (256^3, whole: 43.6 us against 44.8; 512^3: 272.5
+// against 269.7).  The others take 4, whose workgroups end sooner: float32
+// ABS 182.2 against 188.8 with 8 (512^3); float64 ABS pass 1 109 against 112
+// (384^3).  The pack plan takes 8 (kStageWaves).
 constexpr int kStageWaves = 8;
-template <typename T> constexpr int stage_waves() { return sizeof(T) == 4 ? 8 : 4; }
+template <typename T, int Q> constexpr int stage_waves() {
+  return sizeof(T) == 4 && (is_rel_q<Q>() || Q == kNOA) ? 8 : 4;
+}
 
 // look-back state word: 2-bit flag | 62-bit count
 constexpr uint64_t kFlagAgg = 1ull << 62;   // the tile's own outlier count

@@ -51,17 +51,21 @@ def test_small_field_limits(dt, q, n):
         assert first_diff(_gpu_stream(q, x, 1e-3), O.quantize(q, x, 1e-3)) is None, kind
 
 
-# 2048 pass-1 workgroups of 8 (float32) or 4 (float64) chunks, and one more
-@pytest.mark.parametrize("dt,n", [(np.float32, 2048 * 8 * 1024), (np.float32, 2048 * 8 * 1024 + 1),
-                                  (np.float64, 2048 * 4 * 1024), (np.float64, 2048 * 4 * 1024 + 1)])
-def test_totals_limit(dt, n):
+# 4096 pass-1 workgroups of 8 (float32 REL) or 4 chunks, and one more
+@pytest.mark.parametrize("q,dt,n", [("rel", np.float32, 4096 * 8 * 1024),
+                                    ("rel", np.float32, 4096 * 8 * 1024 + 1),
+                                    ("abs", np.float32, 4096 * 4 * 1024),
+                                    ("abs", np.float32, 4096 * 4 * 1024 + 1),
+                                    ("abs", np.float64, 4096 * 4 * 1024),
+                                    ("abs", np.float64, 4096 * 4 * 1024 + 1)])
+def test_totals_limit(q, dt, n):
     x = synth.sines_1d(n, 11, dtype=dt)
     x[::977] = np.nan              # about one per chunk
     x[n // 2: n // 2 + 40 * 1024: 9] = np.nan    # 114 per chunk
     x[n // 4: n // 4 + 300 * 1024: 3] = np.nan   # 342 per chunk: over either stage cap
     x[n - 700:] = np.nan
-    announce("totals limit", np.dtype(dt).name, n)
-    assert first_diff(_gpu_stream("abs", x, 1e-3), O.quantize_mt("abs", x, 1e-3)) is None
+    announce("totals limit", q, np.dtype(dt).name, n)
+    assert first_diff(_gpu_stream(q, x, 1e-3), O.quantize_mt(q, x, 1e-3)) is None
 
 
 # compress: 2048 workgroups of 4 chunks, and one more
