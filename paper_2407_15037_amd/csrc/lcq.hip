@@ -4,12 +4,20 @@
 // batched path (lcq_batch.hip).
 //
 // Kernels (all memory-bound; no MFMA, nothing here is a contraction):
-//   k_clear        zero the look-back state before a quantize (ABS / REL)
-//   k_minmax       NOA pass 1 (lcq_range.hpp): finite min / max per
-//                  workgroup (section 2.1.3); also zeroes the look-back state
-//   k_noa_params   NOA pass 2 (lcq_range.hpp, one workgroup): reduce the
+//   k_quant_small  small fields (lcq_chunk.hpp): everything below in one
+//                  workgroup and one launch
+//   k_clear        zero the look-back state (tile variants) or the group sums
+//                  (large fields) before a quantize (ABS / REL)
+//   k_minmax       NOA range (lcq_range.hpp): finite min / max per
+//                  workgroup (section 2.1.3); also does k_clear's work
+//   k_noa_params   large NOA fields (lcq_range.hpp, one workgroup): reduce the
 //                  per-workgroup results and derive ebR, step, 1/step on the
-//                  device
+//                  device (otherwise k_quant_stage's wavefronts do)
+//   k_quant_stage, k_quant_finish
+//                  the default two-pass quantize (lcq_chunk.hpp): one
+//                  wavefront per 1024-value chunk
+//   k_dequantize_chunks
+//                  the default dequantize (lcq_chunk.hpp)
 //   k_quantize     one tile per workgroup, tile = workgroup index (no atomic
 //                  counter): quant_tile (classify / bin / reconstruct / verify,
 //                  code stores, in-tile ranks, bounded decoupled look-back,
@@ -134,7 +142,7 @@ struct StageQ {
   void *stage;
   uint32_t *totals;           // one per pass-1 workgroup, or null:
   unsigned long long *group;  // one per group
-  uint64_t tiles_per_group, chunks_per_group, ngroups;
+  uint64_t ntiles, tiles_per_group, chunks_per_group, ngroups;
   DevParams *noa;
   const void *partials;  // NOA, nparts > 0: range pairs pass 1 still has to reduce
   unsigned nparts;
@@ -188,6 +196,7 @@ __global__ __launch_bounds__(kBlock) void k_quant_finish(StageQ a) {
   f.stage = static_cast<const U *>(a.stage);
   f.totals = a.totals;
   f.group = a.group;
+  f.ntiles = a.ntiles;
   f.tiles_per_group = a.tiles_per_group;
   f.chunks_per_group = a.chunks_per_group;
   f.ngroups = a.ngroups;
@@ -484,6 +493,7 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
     sq.counts = reinterpret_cast<uint16_t *>(ws + ws_counts_off());
     sq.stage = ws + ws_stage_off(n);
     sq.group = reinterpret_cast<unsigned long long *>(ws + kWsState);
+    sq.ntiles = a.ntiles;
     sq.tiles_per_group = tiles_per_group(a.ntiles, tile / kChunk, kGroupChunksAlone);
     if (a.ntiles <= kMaxDirectTiles) {
       sq.totals = reinterpret_cast<uint32_t *>(ws + ws_totals_off(n));

@@ -345,6 +345,7 @@ __device__ __forceinline__ void finish_item(const BatchQArgs &a, const BField &b
   f.stage = reinterpret_cast<const U *>(a.ws + bf.stage_off);
   f.totals = nullptr;
   f.group = reinterpret_cast<const unsigned long long *>(a.ws + bf.group_off);
+  f.ntiles = bf.ntiles;
   f.tiles_per_group = bf.tiles_per_group;
   f.chunks_per_group = bf.chunks_per_group;
   f.ngroups = bf.ngroups;

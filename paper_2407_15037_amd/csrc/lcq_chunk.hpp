@@ -403,6 +403,7 @@ template <typename T> struct FinishField {
   const typename FT<T>::U *stage;
   const uint32_t *totals;  // pass-1 workgroups' counts, or null:
   const unsigned long long *group;
+  uint64_t ntiles;           // (with totals)
   uint64_t tiles_per_group;  // (with totals: a multiple of 4)
   uint64_t chunks_per_group;
   uint64_t ngroups;
@@ -487,6 +488,27 @@ __device__ __forceinline__ void copy_rows(const typename FT<T>::U *stage, typena
   }
 }
 
+// The staged row of chunk c (cnt <= stage cap outliers) to outl from index
+// P on.  One wavefront; every load is issued before the first store.
+template <typename T>
+__device__ __forceinline__ void copy_staged(const FinishField<T> &f, typename FT<T>::U *outl,
+                                            uint64_t c, uint64_t P, unsigned cnt, int lane) {
+  using U = typename FT<T>::U;
+  constexpr unsigned kCap = (unsigned)stage_cap<T>();
+  constexpr int kR = (int)kCap / 64;
+  U v[kR];
+#pragma unroll
+  for (int r = 0; r < kR; r++) {
+    const unsigned i = (unsigned)lane + 64u * r;
+    v[r] = f.stage[c * kCap + min(i, cnt - 1)];
+  }
+#pragma unroll
+  for (int r = 0; r < kR; r++) {
+    const unsigned i = (unsigned)lane + 64u * r;
+    if (i < cnt) outl[P + i] = v[r];
+  }
+}
+
 static_assert(LCQ_MAX_N / kChunk <= 0xFFFFFFFFull, "chunk indices fit 32 bits");
 
 // Index of chunk c's first outlier, from the pass-1 group sums (with totals:
@@ -558,12 +580,33 @@ __device__ void group_prefix(const FinishField<T> &f, unsigned *s_grp, unsigned 
   __syncthreads();
 }
 
+// A group with far more outliers than the average one (a stretch of hard
+// data in an otherwise smooth field) is hot: its chunks with more than
+// kDirect outliers are left to all workgroups.  Fields that are hard
+// everywhere have no hot group: there each workgroup's own batch is an even
+// share already.
+constexpr unsigned kDirect = 32;
+__device__ __forceinline__ uint64_t hot_limit(uint64_t all, uint64_t ngroups) {
+  return 4 * ((uint32_t)ngroups ? all / (uint32_t)ngroups : 0) + 6144;
+}
+// Outliers of group G.
+template <typename T>
+__device__ __forceinline__ uint64_t group_outliers(const FinishField<T> &f, uint64_t G) {
+  if (!f.totals) return f.group[G];
+  // (called for groups of chunks that exist: with totals past the last
+  // workgroup masked)
+  const uint64_t t1 = min((G + 1) * f.tiles_per_group, f.ntiles);
+  unsigned s = 0;
+  for (uint64_t t = G * f.tiles_per_group; t < t1; t++) s += f.totals[t];
+  return s;
+}
+
 // Pass 2 for group g: chunk-table entries of its chunks, their outliers,
 // and (last group) header, padding and stream size.
 template <typename T>
 __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   using U = typename FT<T>::U;
-  __shared__ unsigned long long s_red[kWaves];
+  __shared__ unsigned long long s_red[2][kWaves];
   __shared__ unsigned s_wt[kWaves];
   __shared__ unsigned s_P[kBlock];
   __shared__ unsigned s_c[kBlock];
@@ -587,34 +630,50 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   // outliers of all earlier groups: every load issued before the first add
   // (unconditional loads at a clamped index, masked afterwards)
   static_assert(kMaxGroups % kBlock == 0, "whole rounds of group sums");
-  unsigned long long b = 0;
+  unsigned long long b = 0, all = 0;  // before this group, and of all groups
   if (f.totals) {
     const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
-    const unsigned m = (unsigned)(g * f.tiles_per_group / 4);
-    unsigned t = 0;
+    const unsigned m = (unsigned)(g * f.tiles_per_group), nt = (unsigned)f.ntiles;
+    unsigned t = 0, ta = 0;
     static_assert(kMaxDirectTiles == 16 * kBlock, "four loads of four per thread");
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const unsigned i = (unsigned)(tid + k * kBlock);
-      const nt_i4 v = tot[i < m ? i : 0];
-      const unsigned q = (unsigned)v.x + (unsigned)v.y + (unsigned)v.z + (unsigned)v.w;
-      t += i < m ? q : 0u;
+      const nt_i4 v = tot[4 * i < nt ? i : 0];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {  // (words past the last workgroup's are garbage)
+        const unsigned w = 4 * i + u < nt ? (unsigned)v[u] : 0u;
+        t += 4 * i + u < m ? w : 0u;
+        ta += w;
+      }
     }
+    all = ta;
     b = t;
   } else {
 #pragma unroll
     for (int k = 0; k < (int)(kMaxGroups / kBlock); k++) {
       const uint64_t i = (uint64_t)tid + (uint64_t)k * kBlock;
-      const unsigned long long v = f.group[i < g ? i : 0];
+      const unsigned long long v = f.group[i < f.ngroups ? i : 0];
       b += i < g ? v : 0ull;
+      all += i < f.ngroups ? v : 0ull;
     }
   }
+  const uint64_t own = group_outliers<T>(f, g);
   b = wave_sum(b);
-  if (lane == 0) s_red[wave] = b;
+  all = wave_sum(all);
+  if (lane == 0) {
+    s_red[0][wave] = b;
+    s_red[1][wave] = all;
+  }
   __syncthreads();
-  uint64_t run = 0;
+  uint64_t run = 0, grand = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; w++) run += s_red[w];
+  for (int w = 0; w < kWaves; w++) {
+    run += s_red[0][w];
+    grand += s_red[1][w];
+  }
+  const uint64_t lim = hot_limit(grand, f.ngroups);
+  const bool hot = own > lim;  // uniform
 
   for (uint64_t cb = c0; cb < c1; cb += kBlock) {
     const uint64_t c = cb + tid;
@@ -634,21 +693,35 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     s_P[tid] = (unsigned)before + (incl - cnt);  // batch-relative first outlier of each chunk
     s_c[tid] = cnt;                              // (read after the barrier below)
     __syncthreads();  // s_P and s_c whole
-    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
+    if (hot) {  // only the short rows here, one wavefront each
+      for (int i = wave; i < kBlock; i += kWaves) {
+        const unsigned ci = __builtin_amdgcn_readfirstlane(s_c[i]);
+        if (ci <= kDirect && (unsigned)lane < ci)
+          outl[run + s_P[i] + (unsigned)lane] = f.stage[(cb + (uint64_t)i) * kCap + lane];
+      }
+    } else {
+      copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
+    }
     run += total;
     __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
   }
 
-  // Chunks with more outliers than were staged are finished not by their
-  // own group: workgroup g takes chunks g, g + ngroups, g + 2 ngroups, ... so
-  // that runs of such chunks (a stretch of hard data) spread over every
-  // workgroup instead of queueing behind one.  One wavefront per such chunk
-  // finds its outliers again from its codes and input.
+  // Chunks with more outliers than were staged, and those with more than
+  // kDirect of a hot group, are finished not by their own group: workgroup g
+  // takes chunks g, g + ngroups, g + 2 ngroups, ... so that runs of such chunks
+  // (a stretch of hard data) spread over every workgroup instead of queueing
+  // behind one (384^3 float64 ABS with 1024 consecutive chunks of 200
+  // outliers: pass 2 27 us when each group copied its own).  One wavefront
+  // per such chunk copies its staged row or, past the stage cap, finds its
+  // outliers again from its codes and input.
   bool have_grp = false;
   for (uint64_t t0 = 0; g + t0 * f.ngroups < nch; t0 += kBlock) {
     const uint64_t c = g + (t0 + (uint64_t)tid) * f.ngroups;
     const unsigned cn = t0 == 0 ? duty0 : (c < nch ? f.counts[c] : 0u);
-    const bool ov = cn > kCap;
+    // (chunk indices fit 32 bits)
+    const bool ov = cn > kCap ||
+                    (cn > kDirect &&
+                     group_outliers<T>(f, (uint32_t)c / (uint32_t)f.chunks_per_group) > lim);
     if (!__syncthreads_or(ov)) continue;
     if (f.totals && !have_grp) {  // uniform
       group_prefix<T>(f, s_grp, s_wt);
@@ -663,12 +736,18 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
       if (w < wave) base += s_wt[w];
       nov += s_wt[w];
     }
-    if (ov) s_P[base + lanes_below(wb, 0u)] = (unsigned)c;  // compact list of this batch's chunks
+    if (ov) {  // compact list of this batch's chunks and their counts
+      s_P[base + lanes_below(wb, 0u)] = (unsigned)c;
+      s_c[base + lanes_below(wb, 0u)] = cn;
+    }
     __syncthreads();
     for (unsigned i = (unsigned)wave; i < nov; i += kWaves) {
       const uint64_t cv = s_P[i];
       const int ln = pin_v(lane);  // (positions recomputed, not held for the whole kernel)
-      rescan_chunk<T>(f, outl, cv, chunk_first_outlier<T>(f, cv, ln, s_grp), ln);
+      const uint64_t P = chunk_first_outlier<T>(f, cv, ln, s_grp);
+      const unsigned cc = __builtin_amdgcn_readfirstlane(s_c[i]);
+      if (cc <= kCap) copy_staged<T>(f, outl, cv, P, cc, ln);
+      else rescan_chunk<T>(f, outl, cv, P, ln);
     }
     __syncthreads();  // s_wt, s_P and s_c are rewritten by the next batch
   }
