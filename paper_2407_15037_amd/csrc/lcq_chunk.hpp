@@ -586,8 +586,10 @@ __device__ void group_prefix(const FinishField<T> &f, unsigned *s_grp, unsigned 
 // everywhere have no hot group: there each workgroup's own batch is an even
 // share already.
 constexpr unsigned kDirect = 32;
-__device__ __forceinline__ uint64_t hot_limit(uint64_t all, uint64_t ngroups) {
-  return 4 * ((uint32_t)ngroups ? all / (uint32_t)ngroups : 0) + 6144;
+// (own: the group's outliers, all: the field's; own > 4 all / ngroups + 6144
+// without the 64-bit division, which is built on fused multiply-adds)
+__device__ __forceinline__ bool hot_group(uint64_t own, uint64_t all, uint64_t ngroups) {
+  return own > 6144 && (own - 6144) * ngroups > 4 * all;
 }
 // Outliers of group G.
 template <typename T>
@@ -672,8 +674,7 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     run += s_red[0][w];
     grand += s_red[1][w];
   }
-  const uint64_t lim = hot_limit(grand, f.ngroups);
-  const bool hot = own > lim;  // uniform
+  const bool hot = hot_group(own, grand, f.ngroups);  // uniform
 
   for (uint64_t cb = c0; cb < c1; cb += kBlock) {
     const uint64_t c = cb + tid;
@@ -721,7 +722,8 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     // (chunk indices fit 32 bits)
     const bool ov = cn > kCap ||
                     (cn > kDirect &&
-                     group_outliers<T>(f, (uint32_t)c / (uint32_t)f.chunks_per_group) > lim);
+                     hot_group(group_outliers<T>(f, (uint32_t)c / (uint32_t)f.chunks_per_group),
+                               grand, f.ngroups));
     if (!__syncthreads_or(ov)) continue;
     if (f.totals && !have_grp) {  // uniform
       group_prefix<T>(f, s_grp, s_wt);
