@@ -695,9 +695,9 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     s_c[tid] = cnt;                              // (read after the barrier below)
     __syncthreads();  // s_P and s_c whole
     if (hot) {  // only the short rows here, one wavefront each
-      for (int i = wave; i < kBlock; i += kWaves) {
-        const unsigned ci = __builtin_amdgcn_readfirstlane(s_c[i]);
-        if (ci <= kDirect && (unsigned)lane < ci)
+      for (uint64_t mk = __ballot(cnt != 0 && cnt <= kDirect); mk; mk &= mk - 1) {
+        const int l = __ffsll((unsigned long long)mk) - 1, i = wave * 64 + l;
+        if ((unsigned)lane < s_c[i])
           outl[run + s_P[i] + (unsigned)lane] = f.stage[(cb + (uint64_t)i) * kCap + lane];
       }
     } else {
