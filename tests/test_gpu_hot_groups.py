@@ -1,0 +1,137 @@
+"""Quantize pass 2 where a stretch of hard data lies in a smooth field: groups
+of chunks with far more outliers than the average one, that hold short rows
+(1 to 32 outliers), longer ones (33 to the stage cap, the cap itself among
+them) and chunks over the cap side by side, the field's ragged last chunk
+among them; and such chunks in groups that are not hot.  With totals per
+first-pass workgroup and with sums per group; alone and in a batch.  The
+oracle's own counts show that the inputs are what they are meant to be."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from gpu_util import announce, first_diff
+
+CHUNK = 1024
+CAP = {np.float32: 128, np.float64: 256}
+EB = 1e-3
+
+
+def layout(q, dt, nch, batch_cpw=0):
+    """(chunks per group, groups) of pass 2 for a field of nch chunks."""
+    if batch_cpw:
+        per_tile, at_least, totals = 4 * batch_cpw, 64, False
+    else:
+        per_tile = 8 if dt == np.float32 and q != "abs" else 4
+        at_least, totals = 16, -(-nch // per_tile) <= 4096
+    tiles = -(-nch // per_tile)
+    tpg = max(-(-at_least // per_tile), -(-tiles // 1024))
+    if totals:
+        tpg = -(-tpg // 4) * 4
+    return tpg * per_tile, -(-tiles // tpg)
+
+
+def hard_field(dt, cpg, ngroups, seed):
+    """A smooth field of ngroups whole groups of cpg chunks (the last chunk 24
+    values short) with hot groups 1, ngroups // 2 and the last, and a group
+    of mixed rows that is not hot."""
+    rng = np.random.default_rng(seed)
+    cap = CAP[dt]
+    n = cpg * ngroups * CHUNK - 24
+    x = np.resize(synth.sines_1d(1 << 18, seed, dtype=dt), n)
+
+    def rows(g, counts):
+        for i, k in enumerate(counts):
+            c = (g * cpg + i) * CHUNK
+            v = x[c: c + CHUNK]
+            v[:] = 0.5
+            v[rng.permutation(v.size)[: min(k, v.size)]] = np.nan
+
+    mixed = [31, 32, 33, 1, 0, 64, cap, cap + 1]
+    for g in (1, ngroups // 2, ngroups - 1):
+        rows(g, mixed + [CHUNK] * 8)
+    rows(ngroups // 3, mixed)
+    if cpg > 16:  # the ragged chunk is far from the rows above
+        x[-(CHUNK - 24):] = np.nan
+    return x
+
+
+def check_input(st, dt, n, cpg, ngroups):
+    """The groups are hot, or not, and hold what they should, by the stream's
+    chunk table."""
+    cap = CAP[dt]
+    nch = -(-n // CHUNK)
+    assert nch == cpg * ngroups
+    k = int(st[16:24].view(np.uint64)[0])
+    at = (64 + 4 * n + 15) // 16 * 16
+    table = np.append(st[at: at + 8 * nch].view(np.uint64).astype(np.int64), k)
+    cnt = np.diff(table).reshape(ngroups, cpg)
+    own = cnt.sum(axis=1)
+    hot = np.flatnonzero((own > 6144) & ((own - 6144) * ngroups > 4 * k))
+    assert list(hot) == [1, ngroups // 2, ngroups - 1], hot
+    for g in hot:
+        assert {31, 32, 33, 1, 0, 64, cap, cap + 1} <= set(cnt[g]), cnt[g]
+    assert cnt[-1, -1] == CHUNK - 24
+    cold = cnt[ngroups // 3]
+    assert {31, 32, 33, cap, cap + 1} <= set(cold), cold
+
+
+# groups of 16 and 32 chunks with totals; just past 4096 first-pass workgroups,
+# groups of 20 and 40 chunks with group sums
+ALONE = [("abs", np.float32, 150), ("rel", np.float32, 150), ("noa", np.float32, 150),
+         ("abs", np.float64, 150), ("rel", np.float64, 150), ("noa", np.float64, 150),
+         ("abs", np.float32, 820), ("rel", np.float32, 820), ("abs", np.float64, 820)]
+
+
+def alone(q, dt, ngroups):
+    waves = 8 if dt == np.float32 and q != "abs" else 4
+    tiles = ngroups * 5 if ngroups > 800 else ngroups * 4
+    cpg, ng = layout(q, dt, tiles * waves)
+    assert ng == ngroups and (tiles <= 4096) == (ngroups < 800)
+    x = hard_field(dt, cpg, ng, 31)
+    st = O.quantize_mt(q, x, EB)
+    check_input(st, dt, x.size, cpg, ng)
+    return x, st
+
+
+@pytest.mark.parametrize("q,dt,ngroups", [a for a in ALONE if a[2] < 800])
+def test_inputs(q, dt, ngroups):
+    alone(q, dt, ngroups)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("q,dt,ngroups", ALONE)
+def test_hot_groups(q, dt, ngroups):
+    import torch
+    import paper_2407_15037_amd as lcq
+    x, want = alone(q, dt, ngroups)
+    xt = torch.from_numpy(x).cuda()
+    ws = torch.full((lcq.workspace_bytes(q, xt.dtype, x.size),), 0xA5, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((lcq.max_stream_bytes(xt.dtype, x.size),), 0x5A, dtype=torch.uint8,
+                     device="cuda")
+    announce("hot groups", q, np.dtype(dt).name, x.size)
+    buf, nb = lcq.quantize(xt, q, EB, out=out, ws=ws)
+    assert first_diff(buf[: int(nb.item())].cpu().numpy(), want) is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cpw", [1, 4])
+def test_hot_groups_in_a_batch(cpw):
+    import torch
+    from paper_2407_15037_amd.batch import BatchPlan
+    fields, want = [], []
+    for q, dt in (("abs", np.float32), ("rel", np.float32), ("noa", np.float64)):
+        cpg, ng = layout(q, dt, 64 * 100, cpw)
+        assert (cpg, ng) == (64, 100)
+        x = hard_field(dt, cpg, ng, 33)
+        st = O.quantize_mt(q, x, EB)
+        check_input(st, dt, x.size, cpg, ng)
+        fields.append({"x": torch.from_numpy(x).cuda(), "q": q, "eb": EB})
+        want.append(st)
+    announce("hot groups in a batch", cpw)
+    plan = BatchPlan(fields, tune=f"batch=0 f32={cpw} f64={cpw}")
+    plan.quantize()
+    for f, st in zip(plan.fields, want):
+        got = f["stream"][: int(f["nbytes"].item())].cpu().numpy()
+        assert first_diff(got, st) is None
