@@ -442,20 +442,21 @@ __device__ void rescan_chunk(const FinishField<T> &f, typename FT<T>::U *outl, u
   }
 }
 
-// The staged rows of a pass-2 workgroup's chunks to their places, one
-// outlier per thread: outlier t of the batch's `total` belongs to the chunk i
-// with s_P[i] <= t < s_P[i + 1] (found by bisection of the kBlock prefixes in
-// LDS; chunks past the batch's end hold `total`) and is entry t - s_P[i] of
-// its row.  Outliers of chunks over the stage cap are left out.  Reads follow
-// the rows, writes are contiguous, a batch without outliers costs nothing,
-// and the work is spread evenly whatever the counts: chunk by chunk, with
-// rows of more than 32 taken by one wavefront after another, this took 24 of
-// the 29 us of pass 2 for a 3 M value float32 REL field at 1e-5 (about 100
-// outliers in every chunk).  Short loops on purpose: unrolled over 16 rows
+// The staged rows that a pass-2 workgroup moves for its own chunks to their
+// places, one outlier per thread: outlier t of the batch's `total` belongs to
+// the chunk i with s_S[i] <= t < s_S[i + 1] (found by bisection of the kBlock
+// prefixes in LDS; chunks past the batch's end hold `total`), is entry
+// t - s_S[i] of its row and goes s_L[i] places further than t: the outliers
+// of earlier chunks that are finished elsewhere, which s_S leaves out.  Reads
+// follow the rows, writes are contiguous, a batch without outliers costs
+// nothing, and the work is spread evenly whatever the counts: chunk by chunk,
+// with rows of more than 32 taken by one wavefront after another, this took
+// 24 of the 29 us of pass 2 for a 3 M value float32 REL field at 1e-5 (about
+// 100 outliers in every chunk).  Short loops on purpose: unrolled over 16 rows
 // the kernel's instruction fetch cost more than the loads it overlapped.
 template <typename T>
 __device__ __forceinline__ void copy_rows(const typename FT<T>::U *stage, typename FT<T>::U *out,
-                                          const unsigned *s_P, const unsigned *s_c,
+                                          const unsigned *s_S, const unsigned *s_L,
                                           unsigned total) {
   using U = typename FT<T>::U;
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
@@ -471,20 +472,17 @@ __device__ __forceinline__ void copy_rows(const typename FT<T>::U *stage, typena
 #pragma nounroll
     for (unsigned step = kBlock / 2; step; step >>= 1) {
 #pragma unroll
-      for (int u = 0; u < kRound; u++) i[u] += s_P[i[u] + step] <= t[u] ? step : 0u;
+      for (int u = 0; u < kRound; u++) i[u] += s_S[i[u] + step] <= t[u] ? step : 0u;
     }
     U v[kRound];
-    unsigned ok = 0;
 #pragma unroll
     for (int u = 0; u < kRound; u++) {
-      // (an outlier not staged reads some word of its chunk's row)
-      const unsigned r = min(t[u] - s_P[i[u]], kCap - 1);
-      v[u] = stage[i[u] * kCap + r];
-      ok |= (s_c[i[u]] <= kCap && t0 + (unsigned)(u * kBlock) < total ? 1u : 0u) << u;
+      v[u] = stage[i[u] * kCap + (t[u] - s_S[i[u]])];
+      i[u] = s_L[i[u]];
     }
 #pragma unroll
     for (int u = 0; u < kRound; u++)
-      if ((ok >> u) & 1u) out[t[u]] = v[u];
+      if (t0 + (unsigned)(u * kBlock) < total) out[t[u] + i[u]] = v[u];
   }
 }
 
@@ -614,6 +612,7 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   __shared__ unsigned s_c[kBlock];
   __shared__ unsigned s_grp[kMaxGroups];
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
+  constexpr unsigned kScanBits = 17, kScanMask = (1u << kScanBits) - 1;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t n = f.n;
@@ -680,29 +679,34 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     const uint64_t c = cb + tid;
     const unsigned cnt = cnt_next;
     cnt_next = cb + kBlock + tid < c1 ? f.counts[cb + kBlock + tid] : 0u;
-    const unsigned incl = wave_incl_add(cnt);
+    // two prefixes from one scan: all outliers, and those moved here (chunks
+    // left to other workgroups, below, would only be searched and dropped: for
+    // a 512^3 float32 field with every value lossless pass 2 took 556 us with
+    // them, 397 without)
+    const unsigned mine = cnt <= (hot ? kDirect : kCap) ? cnt : 0u;
+    static_assert(64 * kChunk < 1u << kScanBits && 64ull * kCap < 1ull << (32 - kScanBits),
+                  "a wavefront's two sums fit one word");
+    const unsigned incl = wave_incl_add(cnt | mine << kScanBits);
     if (lane == 63) s_wt[wave] = incl;
     __syncthreads();
-    uint64_t before = 0, total = 0;
+    unsigned before = 0, total = 0, mbefore = 0, mtotal = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; w++) {
-      if (w < wave) before += s_wt[w];
-      total += s_wt[w];
-    }
-    const uint64_t P = run + before + (incl - cnt);
-    if (c < c1) chunk_tab[c] = P;
-    s_P[tid] = (unsigned)before + (incl - cnt);  // batch-relative first outlier of each chunk
-    s_c[tid] = cnt;                              // (read after the barrier below)
-    __syncthreads();  // s_P and s_c whole
-    if (hot) {  // only the short rows here, one wavefront each
-      for (uint64_t mk = __ballot(cnt != 0 && cnt <= kDirect); mk; mk &= mk - 1) {
-        const int l = __ffsll((unsigned long long)mk) - 1, i = wave * 64 + l;
-        if ((unsigned)lane < s_c[i])
-          outl[run + s_P[i] + (unsigned)lane] = f.stage[(cb + (uint64_t)i) * kCap + lane];
+      const unsigned t = s_wt[w] & kScanMask, m = s_wt[w] >> kScanBits;
+      if (w < wave) {
+        before += t;
+        mbefore += m;
       }
-    } else {
-      copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, (unsigned)total);
+      total += t;
+      mtotal += m;
     }
+    before += (incl & kScanMask) - cnt;
+    mbefore += (incl >> kScanBits) - mine;
+    if (c < c1) chunk_tab[c] = run + before;
+    s_P[tid] = mbefore;
+    s_c[tid] = before - mbefore;
+    __syncthreads();  // s_P and s_c whole
+    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, mtotal);
     run += total;
     __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
   }
