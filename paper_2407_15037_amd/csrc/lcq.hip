@@ -197,7 +197,6 @@ __global__ __launch_bounds__(kBlock) void k_quant_finish(StageQ a) {
   f.totals = a.totals;
   f.group = a.group;
   f.ntiles = a.ntiles;
-  f.tiles_per_group = a.tiles_per_group;
   f.chunks_per_group = a.chunks_per_group;
   f.ngroups = a.ngroups;
   f.noa = Q == kNOA ? a.noa : nullptr;
@@ -497,7 +496,7 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
     sq.tiles_per_group = tiles_per_group(a.ntiles, tile / kChunk, kGroupChunksAlone);
     if (a.ntiles <= kMaxDirectTiles) {
       sq.totals = reinterpret_cast<uint32_t *>(ws + ws_totals_off(n));
-      sq.tiles_per_group = (sq.tiles_per_group + 3) / 4 * 4;  // read four at a time
+      sq.tiles_per_group = kDirectTilesPerGroup;
     }
     sq.chunks_per_group = sq.tiles_per_group * (tile / kChunk);
     sq.ngroups = (a.ntiles + sq.tiles_per_group - 1) / sq.tiles_per_group;

@@ -346,7 +346,6 @@ __device__ __forceinline__ void finish_item(const BatchQArgs &a, const BField &b
   f.totals = nullptr;
   f.group = reinterpret_cast<const unsigned long long *>(a.ws + bf.group_off);
   f.ntiles = bf.ntiles;
-  f.tiles_per_group = bf.tiles_per_group;
   f.chunks_per_group = bf.chunks_per_group;
   f.ngroups = bf.ngroups;
   f.noa = bf.q == kNOA ? a.params + bf.noa_idx : nullptr;

@@ -62,6 +62,9 @@ constexpr uint64_t kGroupChunksAlone = 16;
 // operation before), and 16,384 totals summed by each of 1024 pass-2
 // workgroups cost more than the clear (512^3 float32 ABS 195 us against 191).
 constexpr uint64_t kMaxDirectTiles = 4096;
+// There, a group is four pass-1 workgroups (16 or 32 chunks).
+constexpr uint64_t kDirectTilesPerGroup = kMaxDirectTiles / kMaxGroups;
+static_assert(4 * kDirectTilesPerGroup >= kGroupChunksAlone, "groups of kGroupChunksAlone chunks");
 
 // Pass-1 workgroups per pass-2 group for a field of `ntiles` pass-1
 // workgroups of `chunks_per_tile` chunks each: at least min_chunks chunks
@@ -403,8 +406,7 @@ template <typename T> struct FinishField {
   const typename FT<T>::U *stage;
   const uint32_t *totals;  // pass-1 workgroups' counts, or null:
   const unsigned long long *group;
-  uint64_t ntiles;           // (with totals)
-  uint64_t tiles_per_group;  // (with totals: a multiple of 4)
+  uint64_t ntiles;  // (with totals)
   uint64_t chunks_per_group;
   uint64_t ngroups;
   const DevParams *noa;  // NOA: header words 4-7 come from here
@@ -443,46 +445,57 @@ __device__ void rescan_chunk(const FinishField<T> &f, typename FT<T>::U *outl, u
 }
 
 // The staged rows that a pass-2 workgroup moves for its own chunks to their
-// places, one outlier per thread: outlier t of the batch's `total` belongs to
-// the chunk i with s_S[i] <= t < s_S[i + 1] (found by bisection of the kBlock
-// prefixes in LDS; chunks past the batch's end hold `total`), is entry
-// t - s_S[i] of its row and goes s_L[i] places further than t: the outliers
-// of earlier chunks that are finished elsewhere, which s_S leaves out.  Reads
+// places, one outlier per thread, kCopyWindow outliers at a time: each thread
+// writes the number of its chunk into LDS for its share [own0, own1) of the
+// chunk's outliers, as far as they lie in the window; then outlier t (of the
+// batch's `total`) of chunk i = s_own[t] is entry t - s_S[i] of its row and goes
+// s_L[i] places further than t (the outliers of earlier chunks that are
+// finished elsewhere, which the ranks t leave out).  Reads
 // follow the rows, writes are contiguous, a batch without outliers costs
 // nothing, and the work is spread evenly whatever the counts: chunk by chunk,
 // with rows of more than 32 taken by one wavefront after another, this took
 // 24 of the 29 us of pass 2 for a 3 M value float32 REL field at 1e-5 (about
-// 100 outliers in every chunk).  Short loops on purpose: unrolled over 16 rows
-// the kernel's instruction fetch cost more than the loads it overlapped.
+// 100 outliers in every chunk).  (Chunk numbers found by bisection of the
+// prefixes instead, up to seven dependent LDS reads: pass 2 of the 512^3
+// float32 fields 6.8 us ABS and 10.0 REL against 6.5 and 8.7.)  Short loops on
+// purpose: unrolled over 16 rows the kernel's instruction fetch cost more than
+// the loads it overlapped.
+constexpr unsigned kCopyWindow = 2048;
 template <typename T>
 __device__ __forceinline__ void copy_rows(const typename FT<T>::U *stage, typename FT<T>::U *out,
-                                          const unsigned *s_S, const unsigned *s_L,
+                                          const unsigned *s_S, const unsigned *s_L, uint8_t *s_own,
+                                          unsigned chunk, unsigned own0, unsigned own1,
                                           unsigned total) {
   using U = typename FT<T>::U;
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
   constexpr int kRound = 4;  // outliers per thread in flight
+  static_assert(kBlock <= 256, "a batch's chunk numbers fit a byte");
 #pragma nounroll
-  for (unsigned t0 = threadIdx.x; t0 < total; t0 += kBlock * kRound) {
-    unsigned i[kRound], t[kRound];
-#pragma unroll
-    for (int u = 0; u < kRound; u++) {
-      t[u] = min(t0 + (unsigned)(u * kBlock), total - 1);
-      i[u] = 0;
-    }
+  for (unsigned w0 = 0; w0 < total; w0 += kCopyWindow) {  // uniform
+    const unsigned wend = min(total, w0 + kCopyWindow);
+    const unsigned end = min(own1, wend);
 #pragma nounroll
-    for (unsigned step = kBlock / 2; step; step >>= 1) {
+    for (unsigned t = max(own0, w0); t < end; t++) s_own[t - w0] = (uint8_t)chunk;
+    __syncthreads();
+#pragma nounroll
+    for (unsigned t0 = w0 + threadIdx.x; t0 < wend; t0 += kBlock * kRound) {
+      unsigned i[kRound], t[kRound];
 #pragma unroll
-      for (int u = 0; u < kRound; u++) i[u] += s_S[i[u] + step] <= t[u] ? step : 0u;
+      for (int u = 0; u < kRound; u++) {
+        t[u] = min(t0 + (unsigned)(u * kBlock), wend - 1);
+        i[u] = s_own[t[u] - w0];
+      }
+      U v[kRound];
+#pragma unroll
+      for (int u = 0; u < kRound; u++) {
+        v[u] = stage[i[u] * kCap + (t[u] - s_S[i[u]])];
+        i[u] = s_L[i[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < kRound; u++)
+        if (t0 + (unsigned)(u * kBlock) < wend) out[t[u] + i[u]] = v[u];
     }
-    U v[kRound];
-#pragma unroll
-    for (int u = 0; u < kRound; u++) {
-      v[u] = stage[i[u] * kCap + (t[u] - s_S[i[u]])];
-      i[u] = s_L[i[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < kRound; u++)
-      if (t0 + (unsigned)(u * kBlock) < total) out[t[u] + i[u]] = v[u];
+    if (wend < total) __syncthreads();  // (uniform) s_own is rewritten
   }
 }
 
@@ -509,25 +522,86 @@ __device__ __forceinline__ void copy_staged(const FinishField<T> &f, typename FT
 
 static_assert(LCQ_MAX_N / kChunk <= 0xFFFFFFFFull, "chunk indices fit 32 bits");
 
-// Index of chunk c's first outlier, from the pass-1 group sums (with totals:
-// their prefix in s_grp) and chunk counts alone (so any workgroup can find
-// it before the chunk table is written).  One wavefront; uniform result.
+// Exclusive prefix of the groups' outlier counts, in LDS: every workgroup sums
+// them for itself, once, and then has the first outlier and the count of any
+// group without another load.  (Summed anew for each row that is not its own
+// group's, and the sums of such rows' groups loaded for the hot test, pass 2
+// took 2 us longer on a 384^3 float64 field with 1024 consecutive chunks of
+// 200 outliers, and 2.7 us of 11 on one of 8 M values.)
+constexpr int kGroupsPerThread = (int)(kMaxGroups / kBlock);  // consecutive ones
+static_assert(kMaxGroups % kBlock == 0, "whole rounds of group sums");
+struct GroupPrefix {
+  uint64_t at[kGroupsPerThread][kBlock];  // within the wavefront that summed it
+  uint64_t wave[kWaves];                  // the wavefronts' sums
+};
+
+// Fills g but for the barrier after.  Every load is issued before the first
+// add (unconditional loads at a clamped index, masked afterwards).
 template <typename T>
-__device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int lane,
-                                        const unsigned *s_grp) {
-  // chunk and group indices fit 32 bits (n <= LCQ_MAX_N = 2^38)
-  const uint64_t gc = (uint32_t)c / (uint32_t)f.chunks_per_group;
-  unsigned long long s = 0;
-  // eight loads per lane in flight per round (unconditional loads at a
-  // clamped index, masked afterwards)
-  for (uint64_t i0 = (uint64_t)lane; !f.totals && i0 < gc; i0 += 64 * 8) {
+__device__ __forceinline__ void sum_groups(const FinishField<T> &f, GroupPrefix &g) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t v[kGroupsPerThread];  // (a group's count fits 32 bits: n <= 2^38)
+  if (f.totals) {  // uniform
+    const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
+    const unsigned nt = (unsigned)f.ntiles;
+    static_assert(kDirectTilesPerGroup == 4, "a group's totals are one load");
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-      const uint64_t i = i0 + 64 * (uint64_t)k;
-      const unsigned long long v = f.group[i < gc ? i : 0];
-      s += i < gc ? v : 0ull;
+    for (int k = 0; k < kGroupsPerThread; k++) {
+      const unsigned i = (unsigned)(tid * kGroupsPerThread + k);
+      const nt_i4 q = tot[4 * i < nt ? i : 0];
+      v[k] = 0;
+#pragma unroll
+      for (int u = 0; u < 4; u++)  // (words past the last workgroup's are garbage)
+        v[k] += 4 * i + u < nt ? (uint32_t)q[u] : 0u;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kGroupsPerThread; k++) {
+      const unsigned i = (unsigned)(tid * kGroupsPerThread + k);
+      const uint32_t w = (uint32_t)f.group[i < f.ngroups ? i : 0];
+      v[k] = i < f.ngroups ? w : 0u;
     }
   }
+  uint32_t sum = 0;  // (below 2^31)
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; k++) sum += v[k];
+  // a wavefront's sum may take more than 32 bits: its two halves apart
+  const uint64_t incl = ((uint64_t)wave_incl_add(sum >> 16) << 16) + wave_incl_add(sum & 0xFFFFu);
+  uint64_t at = incl - sum;
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; k++) {
+    g.at[k][tid] = at;
+    at += v[k];
+  }
+  if (lane == 63) g.wave[wave] = incl;
+}
+
+// First outlier of group G (G < ngroups); outliers of all groups.
+__device__ __forceinline__ uint64_t group_first(const GroupPrefix &g, uint32_t G) {
+  const uint32_t t = G / kGroupsPerThread;  // the thread that holds it
+  uint64_t s = g.at[G % kGroupsPerThread][t];
+#pragma unroll
+  for (int w = 0; w < kWaves - 1; w++) s += t >= (uint32_t)(64 * (w + 1)) ? g.wave[w] : 0ull;
+  return s;
+}
+__device__ __forceinline__ uint64_t all_outliers(const GroupPrefix &g) {
+  uint64_t s = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; w++) s += g.wave[w];
+  return s;
+}
+
+// Index of chunk c's first outlier, from the groups' prefix and the chunk
+// counts alone (so any workgroup can find it before the chunk table is
+// written).  One wavefront; uniform result.
+template <typename T>
+__device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int lane,
+                                        const GroupPrefix &g) {
+  // chunk and group indices fit 32 bits (n <= LCQ_MAX_N = 2^38)
+  const uint32_t gc = (uint32_t)c / (uint32_t)f.chunks_per_group;
+  uint32_t s = 0;
+  // eight loads per lane in flight per round (unconditional loads at a
+  // clamped index, masked afterwards)
   for (uint64_t i0 = gc * f.chunks_per_group + (uint64_t)lane; i0 < c; i0 += 64 * 8) {
 #pragma unroll
     for (int k = 0; k < 8; k++) {
@@ -536,46 +610,8 @@ __device__ uint64_t chunk_first_outlier(const FinishField<T> &f, uint64_t c, int
       s += i < c ? v : 0u;
     }
   }
-  return wave_sum(s) + (f.totals ? s_grp[gc] : 0u);
-}
-
-// Exclusive prefix of the groups' outlier counts, from the pass-1 workgroups'
-// totals: s_grp[g] = outliers of all groups before g, for ngroups groups.
-// One workgroup; ends with a barrier.  (The totals, and so every prefix, fit
-// 32 bits: kMaxDirectTiles workgroups of at most 8192 values.)
-template <typename T>
-__device__ void group_prefix(const FinishField<T> &f, unsigned *s_grp, unsigned *s_wt) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kPer = (int)(kMaxGroups / kBlock);  // consecutive groups per thread
-  const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
-  const unsigned quads = (unsigned)(f.tiles_per_group / 4);
-  unsigned v[kPer], sum = 0;
-#pragma unroll
-  for (int i = 0; i < kPer; i++) {
-    const unsigned g = (unsigned)(tid * kPer + i);
-    // (whole groups only; nothing follows the last one)
-    const unsigned m = g + 1 < f.ngroups ? quads : 0u;
-    unsigned t = 0;
-    for (unsigned q0 = 0; q0 < m; q0 += 4) {  // four loads in flight, clamped and masked
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const nt_i4 x = tot[g * quads + (q0 + u < m ? q0 + u : 0)];
-        const unsigned y = (unsigned)x.x + (unsigned)x.y + (unsigned)x.z + (unsigned)x.w;
-        t += q0 + u < m ? y : 0u;
-      }
-    }
-    v[i] = sum;
-    sum += t;
-  }
-  const unsigned incl = wave_incl_add(sum);
-  __syncthreads();  // s_wt's readers before
-  if (lane == 63) s_wt[wave] = incl;
-  __syncthreads();
-  unsigned base = incl - sum;
-  for (int w = 0; w < wave; w++) base += s_wt[w];
-#pragma unroll
-  for (int i = 0; i < kPer; i++) s_grp[tid * kPer + i] = base + v[i];
-  __syncthreads();
+  s = wave_sum32(s);
+  return group_first(g, gc) + s;
 }
 
 // A group with far more outliers than the average one (a stretch of hard
@@ -583,22 +619,26 @@ __device__ void group_prefix(const FinishField<T> &f, unsigned *s_grp, unsigned 
 // kDirect outliers are left to all workgroups.  Fields that are hard
 // everywhere have no hot group: there each workgroup's own batch is an even
 // share already.
+// Pass 2 of a float64 ABS field with 1024 consecutive chunks of 200 outliers:
+// of 8 M values 6.4 us with the margin 1024, one turn of copy_rows, 6.4 with 512,
+// 8.0 with 2048, 8.3 with 6144 (384^3: 8.7 and 10.3 with 1024 and 6144); of 2 M
+// values 6.1 with 4 times the average, 6.3 with 2, 7.7 with 8.  Fields whose
+// density of outliers rises and falls over their length do not tell them apart.
 constexpr unsigned kDirect = 32;
-// (own: the group's outliers, all: the field's; own > 4 all / ngroups + 6144
-// without the 64-bit division, which is built on fused multiply-adds)
-__device__ __forceinline__ bool hot_group(uint64_t own, uint64_t all, uint64_t ngroups) {
-  return own > 6144 && (own - 6144) * ngroups > 4 * all;
+constexpr unsigned kHotMargin = 1024;
+// Group G is hot: its outliers > 4 all / ngroups + kHotMargin, without the 64-bit
+// division, which is built on fused multiply-adds (all: the field's outliers).
+__device__ __forceinline__ bool hot_group(const GroupPrefix &g, uint32_t G, uint64_t all,
+                                          uint64_t ngroups) {
+  const uint64_t own = (G + 1 < ngroups ? group_first(g, G + 1) : all) - group_first(g, G);
+  return own > kHotMargin && (own - kHotMargin) * ngroups > 4 * all;
 }
-// Outliers of group G.
-template <typename T>
-__device__ __forceinline__ uint64_t group_outliers(const FinishField<T> &f, uint64_t G) {
-  if (!f.totals) return f.group[G];
-  // (called for groups of chunks that exist: with totals past the last
-  // workgroup masked)
-  const uint64_t t1 = min((G + 1) * f.tiles_per_group, f.ntiles);
-  unsigned s = 0;
-  for (uint64_t t = G * f.tiles_per_group; t < t1; t++) s += f.totals[t];
-  return s;
+
+// log2 of the threads per chunk of a pass-2 workgroup with `chunks` left.
+__device__ __forceinline__ unsigned batch_shift(uint64_t chunks) {
+  static_assert(kBlock == 256, "8 bits of threads");
+  const unsigned m = (unsigned)min<uint64_t>((uint64_t)kBlock, chunks);
+  return 8u - (m > 1 ? 32u - (unsigned)__builtin_clz(m - 1) : 0u);
 }
 
 // Pass 2 for group g: chunk-table entries of its chunks, their outliers,
@@ -606,11 +646,11 @@ __device__ __forceinline__ uint64_t group_outliers(const FinishField<T> &f, uint
 template <typename T>
 __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   using U = typename FT<T>::U;
-  __shared__ unsigned long long s_red[2][kWaves];
   __shared__ unsigned s_wt[kWaves];
   __shared__ unsigned s_P[kBlock];
   __shared__ unsigned s_c[kBlock];
-  __shared__ unsigned s_grp[kMaxGroups];
+  __shared__ uint8_t s_own[kCopyWindow];
+  __shared__ GroupPrefix s_grp;
   constexpr unsigned kCap = (unsigned)stage_cap<T>();
   constexpr unsigned kScanBits = 17, kScanMask = (1u << kScanBits) - 1;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -622,71 +662,39 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
 
   const uint64_t c0 = g * f.chunks_per_group;
   const uint64_t c1 = min(c0 + f.chunks_per_group, nch);
+  // A batch of chunks: up to kBlock of them, the 1 << shift threads of each chunk
+  // in a row (all of them know its count; the first one adds it to the scan).
+  unsigned shift = batch_shift(c1 - c0);
   // the first batch's count (and the first count of the rescan duty below)
   // is loaded before the earlier groups are summed
-  unsigned cnt_next = c0 + tid < c1 ? f.counts[c0 + tid] : 0u;
+  const uint64_t ca = c0 + ((unsigned)tid >> shift);
+  unsigned cnt_next = ca < c1 ? f.counts[ca] : 0u;
   const uint64_t cd0 = g + (uint64_t)tid * f.ngroups;
   const unsigned duty0 = cd0 < nch ? f.counts[cd0] : 0u;
 
-  // outliers of all earlier groups: every load issued before the first add
-  // (unconditional loads at a clamped index, masked afterwards)
-  static_assert(kMaxGroups % kBlock == 0, "whole rounds of group sums");
-  unsigned long long b = 0, all = 0;  // before this group, and of all groups
-  if (f.totals) {
-    const nt_i4 *tot = reinterpret_cast<const nt_i4 *>(f.totals);
-    const unsigned m = (unsigned)(g * f.tiles_per_group), nt = (unsigned)f.ntiles;
-    unsigned t = 0, ta = 0;
-    static_assert(kMaxDirectTiles == 16 * kBlock, "four loads of four per thread");
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const unsigned i = (unsigned)(tid + k * kBlock);
-      const nt_i4 v = tot[4 * i < nt ? i : 0];
-#pragma unroll
-      for (int u = 0; u < 4; u++) {  // (words past the last workgroup's are garbage)
-        const unsigned w = 4 * i + u < nt ? (unsigned)v[u] : 0u;
-        t += 4 * i + u < m ? w : 0u;
-        ta += w;
-      }
-    }
-    all = ta;
-    b = t;
-  } else {
-#pragma unroll
-    for (int k = 0; k < (int)(kMaxGroups / kBlock); k++) {
-      const uint64_t i = (uint64_t)tid + (uint64_t)k * kBlock;
-      const unsigned long long v = f.group[i < f.ngroups ? i : 0];
-      b += i < g ? v : 0ull;
-      all += i < f.ngroups ? v : 0ull;
-    }
-  }
-  const uint64_t own = group_outliers<T>(f, g);
-  b = wave_sum(b);
-  all = wave_sum(all);
-  if (lane == 0) {
-    s_red[0][wave] = b;
-    s_red[1][wave] = all;
-  }
+  sum_groups<T>(f, s_grp);
   __syncthreads();
-  uint64_t run = 0, grand = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; w++) {
-    run += s_red[0][w];
-    grand += s_red[1][w];
-  }
-  const bool hot = hot_group(own, grand, f.ngroups);  // uniform
+  const uint64_t all = all_outliers(s_grp);
+  uint64_t run = group_first(s_grp, (uint32_t)g);
+  const bool hot = hot_group(s_grp, (uint32_t)g, all, f.ngroups);  // uniform
 
   for (uint64_t cb = c0; cb < c1; cb += kBlock) {
-    const uint64_t c = cb + tid;
+    const unsigned i = (unsigned)tid >> shift, part = (unsigned)tid & ((1u << shift) - 1);
     const unsigned cnt = cnt_next;
-    cnt_next = cb + kBlock + tid < c1 ? f.counts[cb + kBlock + tid] : 0u;
     // two prefixes from one scan: all outliers, and those moved here (chunks
     // left to other workgroups, below, would only be searched and dropped: for
     // a 512^3 float32 field with every value lossless pass 2 took 556 us with
     // them, 397 without)
     const unsigned mine = cnt <= (hot ? kDirect : kCap) ? cnt : 0u;
+    const unsigned share = (mine + (1u << shift) - 1) >> shift;  // of the chunk's threads
+    if (cb + kBlock < c1) {  // uniform
+      shift = batch_shift(c1 - cb - kBlock);
+      const uint64_t cn = cb + kBlock + ((unsigned)tid >> shift);
+      cnt_next = cn < c1 ? f.counts[cn] : 0u;
+    }
     static_assert(64 * kChunk < 1u << kScanBits && 64ull * kCap < 1ull << (32 - kScanBits),
                   "a wavefront's two sums fit one word");
-    const unsigned incl = wave_incl_add(cnt | mine << kScanBits);
+    const unsigned incl = wave_incl_add(part == 0 ? cnt | mine << kScanBits : 0u);
     if (lane == 63) s_wt[wave] = incl;
     __syncthreads();
     unsigned before = 0, total = 0, mbefore = 0, mtotal = 0;
@@ -702,11 +710,11 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
     }
     before += (incl & kScanMask) - cnt;
     mbefore += (incl >> kScanBits) - mine;
-    if (c < c1) chunk_tab[c] = run + before;
-    s_P[tid] = mbefore;
-    s_c[tid] = before - mbefore;
-    __syncthreads();  // s_P and s_c whole
-    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, mtotal);
+    if (part == 0 && cb + i < c1) chunk_tab[cb + i] = run + before;
+    s_P[i] = mbefore;
+    s_c[i] = before - mbefore;
+    copy_rows<T>(f.stage + cb * kCap, outl + run, s_P, s_c, s_own, i, mbefore + min(part * share, mine),
+                 mbefore + min((part + 1) * share, mine), mtotal);
     run += total;
     __syncthreads();  // s_wt, s_P, s_c are rewritten by the next batch
   }
@@ -715,24 +723,17 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   // kDirect of a hot group, are finished not by their own group: workgroup g
   // takes chunks g, g + ngroups, g + 2 ngroups, ... so that runs of such chunks
   // (a stretch of hard data) spread over every workgroup instead of queueing
-  // behind one (384^3 float64 ABS with 1024 consecutive chunks of 200
-  // outliers: pass 2 27 us when each group copied its own).  One wavefront
+  // behind one.  One wavefront
   // per such chunk copies its staged row or, past the stage cap, finds its
   // outliers again from its codes and input.
-  bool have_grp = false;
   for (uint64_t t0 = 0; g + t0 * f.ngroups < nch; t0 += kBlock) {
     const uint64_t c = g + (t0 + (uint64_t)tid) * f.ngroups;
     const unsigned cn = t0 == 0 ? duty0 : (c < nch ? f.counts[c] : 0u);
     // (chunk indices fit 32 bits)
     const bool ov = cn > kCap ||
                     (cn > kDirect &&
-                     hot_group(group_outliers<T>(f, (uint32_t)c / (uint32_t)f.chunks_per_group),
-                               grand, f.ngroups));
+                     hot_group(s_grp, (uint32_t)c / (uint32_t)f.chunks_per_group, all, f.ngroups));
     if (!__syncthreads_or(ov)) continue;
-    if (f.totals && !have_grp) {  // uniform
-      group_prefix<T>(f, s_grp, s_wt);
-      have_grp = true;
-    }
     const uint64_t wb = __ballot(ov);
     if (lane == 0) s_wt[wave] = (unsigned)__popcll(wb);
     __syncthreads();
@@ -759,7 +760,7 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
   }
 
   if (g == f.ngroups - 1 && tid == 0)
-    finish_stream<T>(f.stream, f.stream_bytes, n, f.hdr, run, f.noa);
+    finish_stream<T>(f.stream, f.stream_bytes, n, f.hdr, all, f.noa);
 }
 
 // ------------------------------------------------- small fields ---

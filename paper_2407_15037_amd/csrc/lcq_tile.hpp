@@ -102,6 +102,8 @@ __device__ __forceinline__ uint32_t wave_incl_add(uint32_t v) {
 __device__ __forceinline__ uint32_t lane63(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
+// Sum of v over the wavefront (a uniform value).
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) { return lane63(wave_incl_add(v)); }
 
 // A value every lane holds, in scalar registers.
 __device__ __forceinline__ float uniform(float v) {
