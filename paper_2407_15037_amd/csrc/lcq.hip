@@ -404,13 +404,20 @@ void launch_quantize_variant(int v, const PlainQ &a, const StageQ &sq, hipStream
   }
 }
 
+// One launch of deq_chunks, whichever kernel holds it: the ablations' decode
+// runs with as many wavefronts per CU as the decode it is timed against.
+template <typename T, typename K>
+void launch_deq_chunks(K kernel, uint64_t ntiles, const PlainD &a, hipStream_t s) {
+  hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(kBlock), lds_for_waves(deq_waves<T>()),
+                     s, a);
+}
+
 template <typename T, int V>
 void launch_dequantize(uint64_t ntiles, const PlainD &a, hipStream_t s) {
   constexpr Shape sh = kDVariants[V];
   if constexpr (sh.cpw > 0) {
     static_assert(sh.cpw == 1, "one chunk per wavefront");
-    hipLaunchKernelGGL(k_dequantize_chunks<T>, dim3((unsigned)ntiles), dim3(kBlock),
-                       lds_for_waves(deq_waves<T>()), s, a);
+    launch_deq_chunks<T>(k_dequantize_chunks<T>, ntiles, a, s);
   } else {
     hipLaunchKernelGGL((k_dequantize<T, sh.slots, sh.rounds>), dim3((unsigned)ntiles),
                        dim3(kBlock), 0, s, a);
@@ -439,21 +446,19 @@ lcq_status run_quantize(double eb, const void *d_in, uint64_t n, void *d_stream,
   const int v = Q >= kABS_UNCHECKED ? kAblationVariant
                                     : g_variant[0][dt].load(std::memory_order_relaxed);
   const HostParams hp = host_params<T>(Q, eb);
-  if constexpr (Q <= kNOA) {
-    if (n && kQVariants[v].cpw > 0 && n_chunks(n) <= small_chunks<T, Q>()) {
-      SmallQ a{d_in, n, static_cast<uint8_t *>(d_stream), d_bytes,
-               hp.step, hp.inv, hp.bound, hp.low, hp.eb_down,
-               {header_word0(dt, Q), n, 0, __builtin_bit_cast(uint64_t, eb), hp.step, hp.bound,
-                hp.aux0, hp.aux1}};
-      if (g_ev_before) (void)hipEventRecord(g_ev_before, s);
-      if (n_chunks(n) <= kSmallWaves)
-        hipLaunchKernelGGL((k_quant_small<T, Q, 1>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
-      else
-        hipLaunchKernelGGL((k_quant_small<T, Q, kSmallK>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
-      if (g_ev_mid) (void)hipEventRecord(g_ev_mid, s);
-      if (g_ev_after) (void)hipEventRecord(g_ev_after, s);
-      return check_launch();
-    }
+  if (n && kQVariants[v].cpw > 0 && n_chunks(n) <= small_chunks<T, Q>()) {
+    SmallQ a{d_in, n, static_cast<uint8_t *>(d_stream), d_bytes,
+             hp.step, hp.inv, hp.bound, hp.low, hp.eb_down,
+             {header_word0(dt, Q), n, 0, __builtin_bit_cast(uint64_t, eb), hp.step, hp.bound,
+              hp.aux0, hp.aux1}};
+    if (g_ev_before) (void)hipEventRecord(g_ev_before, s);
+    if (n_chunks(n) <= kSmallWaves)
+      hipLaunchKernelGGL((k_quant_small<T, Q, 1>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_quant_small<T, Q, kSmallK>), dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+    if (g_ev_mid) (void)hipEventRecord(g_ev_mid, s);
+    if (g_ev_after) (void)hipEventRecord(g_ev_after, s);
+    return check_launch();
   }
   uint8_t *ws = static_cast<uint8_t *>(d_ws);
   PlainQ a{};
@@ -734,19 +739,15 @@ lcq_status lcq_dequantize_ablation(lcq_ablation kind, lcq_dtype t, const void *d
   a.epoch = g_epoch.fetch_add(1) + 1;
   a.dtype = (int)t;
   const uint64_t tile = deq_tile_len(kAblationVariant);
-  const dim3 grid((unsigned)(n ? (n + tile - 1) / tile : 1));
+  const uint64_t ntiles = n ? (n + tile - 1) / tile : 1;
+  const bool libm = kind == LCQ_ABL_REL_LIBM;
   if (g_ev_before) (void)hipEventRecord(g_ev_before, stream);
-  if (t == LCQ_F32) {
-    if (kind == LCQ_ABL_ABS_UNCHECKED)
-      hipLaunchKernelGGL((k_dequantize_ablation<float, kABS_UNCHECKED>), grid, dim3(kBlock), 0, stream, a);
-    else
-      hipLaunchKernelGGL((k_dequantize_ablation<float, kREL_LIBM>), grid, dim3(kBlock), 0, stream, a);
-  } else {
-    if (kind == LCQ_ABL_ABS_UNCHECKED)
-      hipLaunchKernelGGL((k_dequantize_ablation<double, kABS_UNCHECKED>), grid, dim3(kBlock), 0, stream, a);
-    else
-      hipLaunchKernelGGL((k_dequantize_ablation<double, kREL_LIBM>), grid, dim3(kBlock), 0, stream, a);
-  }
+  if (t == LCQ_F32)
+    launch_deq_chunks<float>(libm ? k_dequantize_ablation<float, kREL_LIBM>
+                                  : k_dequantize_ablation<float, kABS_UNCHECKED>, ntiles, a, stream);
+  else
+    launch_deq_chunks<double>(libm ? k_dequantize_ablation<double, kREL_LIBM>
+                                   : k_dequantize_ablation<double, kABS_UNCHECKED>, ntiles, a, stream);
   if (g_ev_after) (void)hipEventRecord(g_ev_after, stream);
   return check_launch();
 }

@@ -777,9 +777,11 @@ constexpr int kSmallK = 2;  // chunks per wavefront at most
 // two passes take 9-10 us together at these sizes, float64 REL 10.4, NOA's
 // four kernels 15.3; one workgroup takes, at 16 and 32 chunks, 5.0 and 8.3 us
 // for float32 ABS, 6.4 and 11.2 REL, 7.2 and 11.6 NOA; float64 5.8 and 10.0
-// ABS, 8.2 and 15.1 REL, 8.2 and 13.5 NOA).
+// ABS, 8.2 and 15.1 REL, 8.2 and 13.5 NOA).  An ablation goes where its
+// counterpart goes.
 template <typename T, int Q> constexpr uint64_t small_chunks() {
-  return Q == kNOA || (sizeof(T) == 4 && Q == kABS) ? 32 : sizeof(T) == 4 || Q == kABS ? 24 : 18;
+  if (Q == kNOA) return 32;
+  return is_rel_q<Q>() ? (sizeof(T) == 4 ? 24 : 18) : (sizeof(T) == 4 ? 32 : 24);
 }
 
 // Finite minimum and maximum of the chunk's values below len (section 2.1.3;
