@@ -597,23 +597,18 @@ __global__ void k_clear_cmp(uint64_t *p, uint64_t count) {
 // [256, ...)  outliers per group, then record bytes per group (kMaxGroups
 //             each), cleared by every compress
 // then        counts, meta and record sizes (4 bytes per chunk each), the
-//             outlier flags (2 bytes per lane of a chunk), NOA's range pairs
-//             (behind room for stage_cap<T>() values per chunk that earlier
-//             layouts kept: the size callers were told stays).  Counts take
-//             2 of their 4 bytes per chunk; the totals follow them there.
+//             outlier flags (2 bytes per lane of a chunk), NOA's range pairs.
+//             Counts take 2 of their 4 bytes per chunk; the totals follow
+//             them there.
 constexpr uint64_t kCwParams = 64, kCwGroups = 256;
 uint64_t al256(uint64_t v) { return (v + 255) & ~255ull; }
 uint64_t cw_counts_off() { return al256(kCwGroups + 16 * kMaxGroups); }
 uint64_t cw_meta_off(uint64_t C) { return al256(cw_counts_off() + 4 * C); }
 uint64_t cw_sizes_off(uint64_t C) { return al256(cw_meta_off(C) + 4 * C); }
 uint64_t cw_flags_off(uint64_t C) { return al256(cw_sizes_off(C) + 4 * C); }
-uint64_t cw_stage_off(uint64_t C) { return al256(cw_flags_off(C) + 128 * C); }
-uint64_t cw_partials_off(lcq_dtype t, uint64_t C) {
-  const uint64_t cap = t == LCQ_F64 ? 8ull * stage_cap<double>() : 4ull * stage_cap<float>();
-  return al256(cw_stage_off(C) + cap * C);
-}
-uint64_t cw_need(lcq_quantizer q, lcq_dtype t, uint64_t n) {
-  return cw_partials_off(t, n_chunks(n)) + (q == LCQ_NOA ? 16ull * kMinmaxBlocks : 0);
+uint64_t cw_partials_off(uint64_t C) { return al256(cw_flags_off(C) + 128 * C); }
+uint64_t cw_need(lcq_quantizer q, uint64_t n) {
+  return cw_partials_off(n_chunks(n)) + (q == LCQ_NOA ? 16ull * kMinmaxBlocks : 0);
 }
 
 lcq_status check_launch_cmp() { return hipGetLastError() == hipSuccess ? LCQ_OK : LCQ_ERR_HIP; }
@@ -666,7 +661,7 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   uint64_t *clear_ptr = reinterpret_cast<uint64_t *>(a.group);
   const uint64_t clear_count = a.totals ? 0 : 2 * kMaxGroups;
   if (Q == kNOA) {
-    T *partials = reinterpret_cast<T *>(ws + cw_partials_off((lcq_dtype)dt, C));
+    T *partials = reinterpret_cast<T *>(ws + cw_partials_off(C));
     a.partials = partials;
     a.eb_down = hp.eb_down;
     a.nparts = launch_noa_range<T>(static_cast<const T *>(d_in), n, partials, clear_ptr,
@@ -696,7 +691,7 @@ uint64_t lcq_compress_workspace_bytes(lcq_quantizer q, lcq_dtype t, uint64_t n) 
   if ((t != LCQ_F32 && t != LCQ_F64) || (q != LCQ_ABS && q != LCQ_REL && q != LCQ_NOA) ||
       n > LCQ_MAX_N)
     return 0;
-  return cw_need(q, t, n);
+  return cw_need(q, n);
 }
 
 lcq_status lcq_compress(lcq_quantizer q, lcq_dtype t, double eb, const void *d_in, uint64_t n,
@@ -711,7 +706,7 @@ lcq_status lcq_compress(lcq_quantizer q, lcq_dtype t, double eb, const void *d_i
       ((uintptr_t)d_packed_bytes & 7u))
     return LCQ_ERR_ARG;
   if (packed_cap < lcq_pack_max_bytes(t, n)) return LCQ_ERR_CAPACITY;
-  if (ws_bytes < cw_need(q, t, n)) return LCQ_ERR_CAPACITY;
+  if (ws_bytes < cw_need(q, n)) return LCQ_ERR_CAPACITY;
   if (t == LCQ_F32) {
     switch (q) {
       case LCQ_ABS: return run_compress<float, kABS>(eb, d_in, n, d_packed, d_packed_bytes, d_ws, stream);
