@@ -354,10 +354,8 @@ __global__ __launch_bounds__(kBlock) void k_dequantize_inline(PlainD a) {
 //   NOA                   per-workgroup (min, max) pairs after both
 uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
 uint64_t ws_counts_off() { return align256(kWsState + 8 * kMaxGroups); }
-uint64_t ws_totals_off(uint64_t n) { return align16(ws_counts_off() + 2 * n_chunks(n)); }
-// (2 bytes per chunk, aligned to 16, and 4 per at least 4 chunks: within the
-// 4 per chunk, aligned to 256, for any number of chunks)
-uint64_t ws_stage_off(uint64_t n) { return align256(ws_counts_off() + 4 * n_chunks(n)); }
+uint64_t ws_totals_off(uint64_t n) { return ws_counts_off() + totals_at(n_chunks(n)); }
+uint64_t ws_stage_off(uint64_t n) { return ws_counts_off() + counts_area(n_chunks(n)); }
 uint64_t ws_partials_off(lcq_dtype t, uint64_t n) {
   const uint64_t s = t == LCQ_F64 ? 8 : 4;
   const uint64_t tile = t == LCQ_F64 ? kMinTileF64 : kMinTileF32;

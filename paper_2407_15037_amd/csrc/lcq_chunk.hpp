@@ -66,6 +66,27 @@ constexpr uint64_t kMaxDirectTiles = 4096;
 constexpr uint64_t kDirectTilesPerGroup = kMaxDirectTiles / kMaxGroups;
 static_assert(4 * kDirectTilesPerGroup >= kGroupChunksAlone, "groups of kGroupChunksAlone chunks");
 
+// The chunk counts (2 bytes each) and the totals (4 bytes per pass-1 workgroup
+// of at least kWaves chunks, read four at a time) share an area of 4 bytes per
+// chunk, aligned to 256: the totals' place from its start, and where they end.
+// Pass 2's write addresses come from the totals, so nothing else may lie there.
+// (Checked for 256 consecutive numbers of chunks, and that 256 chunks more never
+// take more than the area grows: so for all.)
+constexpr uint64_t counts_area(uint64_t chunks) { return (4 * chunks + 255) / 256 * 256; }
+constexpr uint64_t totals_at(uint64_t chunks) { return (2 * chunks + 15) / 16 * 16; }
+constexpr uint64_t totals_end(uint64_t chunks) {
+  const uint64_t tiles = (chunks + kWaves - 1) / kWaves;
+  return totals_at(chunks) + (4 * tiles + 15) / 16 * 16;
+}
+constexpr bool totals_fit() {
+  for (uint64_t c = 0; c < 256; c++) {
+    if (totals_end(c) > counts_area(c) || totals_at(c) < 2 * c) return false;
+    if (totals_end(c + 256) - totals_end(c) > counts_area(c + 256) - counts_area(c)) return false;
+  }
+  return true;
+}
+static_assert(totals_fit(), "the totals lie between the chunk counts and the next area");
+
 // Pass-1 workgroups per pass-2 group for a field of `ntiles` pass-1
 // workgroups of `chunks_per_tile` chunks each: at least min_chunks chunks
 // per group (fewer, fuller pass-2 workgroups for many small fields), at

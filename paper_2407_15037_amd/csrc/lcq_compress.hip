@@ -603,7 +603,7 @@ __global__ void k_clear_cmp(uint64_t *p, uint64_t count) {
 constexpr uint64_t kCwParams = 64, kCwGroups = 256;
 uint64_t al256(uint64_t v) { return (v + 255) & ~255ull; }
 uint64_t cw_counts_off() { return al256(kCwGroups + 16 * kMaxGroups); }
-uint64_t cw_meta_off(uint64_t C) { return al256(cw_counts_off() + 4 * C); }
+uint64_t cw_meta_off(uint64_t C) { return cw_counts_off() + counts_area(C); }
 uint64_t cw_sizes_off(uint64_t C) { return al256(cw_meta_off(C) + 4 * C); }
 uint64_t cw_flags_off(uint64_t C) { return al256(cw_sizes_off(C) + 4 * C); }
 uint64_t cw_partials_off(uint64_t C) { return al256(cw_flags_off(C) + 128 * C); }
@@ -641,7 +641,7 @@ lcq_status run_compress(double eb, const void *d_in, uint64_t n, void *d_out, ui
   a.rgroup = a.group + kMaxGroups;
   a.ntiles = ntiles;
   if (ntiles && ntiles <= kMaxCmpDirect)
-    a.totals = reinterpret_cast<uint32_t *>(ws + align16(cw_counts_off() + 2 * C));
+    a.totals = reinterpret_cast<uint32_t *>(ws + cw_counts_off() + totals_at(C));
   a.tiles_per_group = tiles_per_group(ntiles, kWaves);
   a.chunks_per_group = a.tiles_per_group * kWaves;
   a.ngroups = std::max<uint64_t>(1, (ntiles + a.tiles_per_group - 1) / a.tiles_per_group);
