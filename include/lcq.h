@@ -147,7 +147,9 @@ void lcq_profile_events(hipEvent_t before, hipEvent_t after);
 /* Measurement hook: when set (non-null), every following two-pass
  * lcq_quantize call from the calling host thread also records `mid` between
  * its two kernels (the streaming pass and the scan pass), so each pass can
- * be timed on its own.  Pass null to clear. */
+ * be timed on its own.  A small field is quantized by one kernel (see
+ * lcq_tune_set); `mid` is then recorded after it, just before `after`.  Pass
+ * null to clear. */
 void lcq_profile_mid_event(hipEvent_t mid);
 
 /* ------------------------------------------------- section 6 ablations --
@@ -167,7 +169,8 @@ void lcq_profile_mid_event(hipEvent_t mid);
  * lcq_dequantize rejects them, lcq_dequantize_ablation decodes exactly the
  * given kind.  Arguments, buffers and errors as for lcq_quantize /
  * lcq_dequantize; the workspace is lcq_workspace_bytes(LCQ_ABS or LCQ_REL,
- * t, n).  Both always use the default (chunk-per-wavefront) kernels. */
+ * t, n).  Both always use the default (chunk-per-wavefront) kernels, launched
+ * as lcq_quantize and lcq_dequantize launch them. */
 typedef enum { LCQ_ABL_ABS_UNCHECKED = 3, LCQ_ABL_REL_LIBM = 4 } lcq_ablation;
 
 lcq_status lcq_quantize_ablation(lcq_ablation kind, lcq_dtype t, double eb,
@@ -378,7 +381,9 @@ lcq_status lcq_serve(const lcq_server_config *cfg, const lcq_request *req, uint3
  * tiles).  Variant 6 (the default): one wavefront per 1024-value chunk;
  * quantize runs two kernels, a streaming pass that writes codes,
  * per-chunk outlier counts and staged outliers, then a scan pass that
- * writes the chunk table, the outliers and the header.  op 0 = quantize,
+ * writes the chunk table, the outliers and the header -- or, for fields of up
+ * to 18 to 32 chunks (by dtype and quantizer), one kernel of one workgroup
+ * that does all of it and leaves the workspace alone.  op 0 = quantize,
  * 1 = dequantize.  Process-wide; the tuner
  * (paper_2407_15037_amd/autotune.py) measures them and sets the fastest.
  * lcq_tune_set returns LCQ_ERR_ARG for a bad op, dtype or variant;

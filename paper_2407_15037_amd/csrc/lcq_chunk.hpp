@@ -790,8 +790,9 @@ __device__ void quant_finish(const FinishField<T> &f, uint64_t g) {
 // outliers and header.  At these sizes the launches are the cost, not the
 // bytes: three (NOA: four) dependent launches took 14-16 us of host time
 // for a field one workgroup streams in a few.  Every value stays in
-// registers from its load to the outlier store (K chunks per wavefront),
-// so nothing is staged and the input is read once, NOA's too.
+// registers from its load to the outlier store (K chunks per wavefront;
+// float64 NOA with two holds 127 and spills one 64-bit operand), so
+// nothing is staged and the input is read once, NOA's too.
 constexpr int kSmallWaves = 16;
 constexpr int kSmallK = 2;  // chunks per wavefront at most
 // Chunks up to which one workgroup is the faster way (kernel durations: the

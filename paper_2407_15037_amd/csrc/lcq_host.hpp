@@ -25,9 +25,21 @@ constexpr unsigned lds_for_waves(unsigned waves, unsigned own = 0) {
   const unsigned share = 163840u / (waves / (unsigned)kWaves) / 1280u * 1280u;
   return share > own ? share - own : 0u;
 }
-// Wavefronts per CU of the dequantize: 24 for float32 (512^3 REL 174.0 us with
-// all 32, 169.8 with 24, 176.0 with 16), 16 for float64 (384^3 REL 118.4 with
-// all, 116.2 with 24, 112.5 with 16; ABS 114.7, 113.0, 112.7).
+// Wavefronts per CU of the dequantize, whatever the quantizer (it stands in the
+// stream's header, which the host has not read).  us per call, up to 2 M values
+// alike:
+//   float32         all 32   24     16         float64         all 32   16
+//   134 M  REL      175.8   171.6  176.4       56.6 M REL      116.7   111.2
+//          ABS      173.6   172.8  171.0              ABS      113.7   111.1
+//          NOA      174.6   175.8  170.7              NOA      114.4   112.1
+//    60 M  REL       80.9    78.6   80.3       30 M   REL       64.3    60.6
+//          ABS       76.8    75.8   75.6              ABS       61.6    60.0
+//          NOA       77.0    76.3   76.4       12 M   REL       27.5    26.2
+//  16.8 M  REL       25.2    24.2   25.1        8 M   REL       18.0    18.4
+//          ABS       22.6    22.3   22.9              ABS       18.1    17.8
+//          NOA       22.8    22.6   23.0        6 M   REL       12.9    15.0
+// (6 M float64 values are 1465 workgroups: one turn with 32, a turn and a half
+// with 16.)
 template <typename T> constexpr unsigned deq_waves() { return sizeof(T) == 4 ? 24u : 16u; }
 
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }

@@ -25,8 +25,8 @@ constexpr int kWaves = kBlock / 64;
 // pass-1 totals, adds to its group's counter on every workgroup, and 8 halve
 // those adds: 188.7 us on the 512^3 field against 193.0 with 4 (16: 249).
 // float32 NOA, whose input the range pass left in the Infinity Cache up to
-// 256 MB, takes 8 as well (256^3, whole: 43.6 us against 44.8; 512^3: 272.5
-// against 269.7).  The others take 4, whose workgroups end sooner: float32
+// 256 MB, takes 8 as well (whole: 16.8 M values 43.2 us against 44.7, 25 M 59.9
+// against 61.5, 33.6 M 75.3 against 76.5; 8.4, 60 and 134 M alike).  The others take 4, whose workgroups end sooner: float32
 // ABS 182.2 against 188.8 with 8 (512^3); float64 ABS pass 1 109 against 112
 // (384^3).  The pack plan takes 8 (kStageWaves).
 constexpr int kStageWaves = 8;
