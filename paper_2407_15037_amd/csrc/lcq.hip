@@ -659,9 +659,10 @@ lcq_status lcq_quantize_noalloc(lcq_quantizer q, lcq_dtype t, double eb, const v
   void *ws = nullptr;
   const lcq_status st = scratch_address(&ws);
   if (st != LCQ_OK) return st;
-  // every word of the workspace a quantize reads is written earlier in the
-  // same call (group sums and look-back words are cleared by its first
-  // kernel), so what the previous call left in the array does not matter
+  // every word of the workspace that a quantize uses is written earlier in the
+  // same call (group sums and look-back words are cleared by its first kernel,
+  // totals stored by pass 1 and what lies behind the last of them masked), so
+  // what the previous call left in the array does not matter
   return lcq_quantize(q, t, eb, d_in, n, d_stream, stream_cap, d_stream_bytes, ws,
                       LCQ_NOALLOC_SCRATCH_BYTES, stream);
 }

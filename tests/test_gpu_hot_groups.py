@@ -166,3 +166,61 @@ def test_hot_groups_in_a_batch(cpw):
     for f, st in zip(plan.fields, want):
         got = f["stream"][: int(f["nbytes"].item())].cpu().numpy()
         assert first_diff(got, st) is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+def test_groups_of_several_batches(dt):
+    """Groups of 300 chunks (307,200 in all): a pass-2 workgroup takes 256 of
+    them, then 44, with 0 to 60 outliers in most, a few over the stage cap and
+    one hot group of short, full and over-cap rows.  Codes, chunk table and
+    outliers follow from the input: every value is either 0.5 or a NaN with its
+    own payload."""
+    import torch
+    import paper_2407_15037_amd as lcq
+    from paper_2407_15037_amd.batch import BatchPlan
+    nch, cap = 300 * 1024, CAP[dt]
+    assert layout("abs", dt, nch) == (300, 1024)
+    g = torch.Generator().manual_seed(9)
+    cnt = torch.randint(0, 61, (nch,), generator=g)
+    over = torch.rand(nch, generator=g) < 0.01
+    cnt[over] = torch.randint(cap + 1, 400, (int(over.sum()),), generator=g)
+    cnt[600 * 300: 601 * 300] = torch.tensor([20, cap, CHUNK] * 100)
+    cnt[-1] = CHUNK
+    own = cnt.reshape(1024, 300).sum(1)
+    assert int(own[600]) > 1024 + 4 * int(own.sum()) // 1024 and int(own[:256].max()) > 2048
+    cnt = cnt.cuda()
+    idt, tdt = ((torch.int32, torch.float32) if dt == np.float32 else (torch.int64, torch.float64))
+    n = nch * CHUNK
+    pos = torch.arange(CHUNK, device="cuda")
+    x = torch.full((nch, CHUNK), 0.5, dtype=tdt, device="cuda")
+    want = []
+    for c0 in range(0, nch, 1 << 14):  # (slices, to keep the index tensors small)
+        c = torch.arange(c0, min(c0 + (1 << 14), nch), device="cuda")
+        mask = (pos[None] * 389 + c[:, None] * 17) % CHUNK < cnt[c][:, None]
+        word = (c[:, None] * CHUNK + pos[None]) & 0x3FFFFF
+        word |= 0x7FC00000 if dt == np.float32 else 0x7FF8000000000000
+        sl = x[c0: c0 + c.numel()].view(idt)
+        sl[mask] = word.to(idt)[mask]
+        want.append(sl[mask])
+    want, x = torch.cat(want), x.reshape(-1)
+    table = torch.cumsum(cnt, 0) - cnt
+    k = int(cnt.sum())
+    ct = (64 + 4 * n + 15) // 16 * 16
+    oo = (ct + 8 * nch + 15) // 16 * 16
+
+    def check(buf, nb):
+        size = int(nb.item())
+        assert size == oo + k * x.element_size()
+        assert int(buf[16:24].view(torch.int64).item()) == k
+        assert torch.equal(buf[ct: ct + 8 * nch].view(torch.int64), table)
+        assert torch.equal(buf[oo: size].view(idt), want)
+        codes = buf[64: 64 + 4 * n].view(torch.int32).reshape(nch, CHUNK)
+        assert torch.equal((codes == -(1 << 31)).sum(1), cnt)
+        assert int(torch.unique(codes[codes != -(1 << 31)]).numel()) == 1
+
+    announce("groups of several batches", np.dtype(dt).name)
+    check(*lcq.quantize(x, "abs", EB))
+    plan = BatchPlan([{"x": x, "q": "abs", "eb": EB}])
+    plan.quantize()
+    check(plan.fields[0]["stream"], plan.fields[0]["nbytes"])
